@@ -371,7 +371,8 @@ lbm_status lbm_get_grid(const lbm_ctx* ctx, int32_t* groups_per_cu, int32_t* gro
  * The call allocates nothing: the per-step scalars (lambda slots, time,
  * event counters) live in a static device array of LBM_NOALLOC_SCRATCH_BYTES
  * bytes that the library holds on each device it runs on until the process
- * ends (one 128-byte record is used).  It does not grow with the grid: any
+ * ends (a 128-byte record and the further records that the launch's waves
+ * spread their updates over).  It does not grow with the grid: any
  * single-instance grid the library accepts (nx, ny < 2^30, nx * ny < 2^32;
  * LBM_EINVAL beyond) runs with it.  Every call on a device shares that
  * device's array and clears it first, so calls that overlap on one device
@@ -382,7 +383,7 @@ lbm_status lbm_get_grid(const lbm_ctx* ctx, int32_t* groups_per_cu, int32_t* gro
  * the stream, fills lambda (lambda^n), a (a^n), t (dt^n), step (1) and the
  * counters of the new state (min_rho, min_rhoe: NaN), and returns the
  * step's first event as lbm_moments does. */
-#define LBM_NOALLOC_SCRATCH_BYTES 256
+#define LBM_NOALLOC_SCRATCH_BYTES 8320
 lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev, void* dst_dev, void* stream,
                             lbm_diag* diag_host);
 

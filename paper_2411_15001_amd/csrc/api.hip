@@ -91,7 +91,7 @@ Scheme make_scheme(const lbm_params* p) {
 }
 
 struct Layout {
-  size_t slots, slots_save, red, insts, items, bndt, bufA, bufB, theta, total;
+  size_t slots, shards, slots_save, red, insts, items, bndt, bufA, bufB, theta, total;
 };
 
 Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
@@ -105,6 +105,8 @@ Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
   size_t o = 0;
   L.slots = o;
   o = align_up(o + sizeof(Slots) * (size_t)n);
+  L.shards = o;  // see Slots
+  o = align_up(o + sizeof(Slots) * (size_t)n * vlbm::kShards);
   L.slots_save = o;  // the adjoint entry points park the slots here
   o = align_up(o + sizeof(Slots));
   L.red = o;  // block partials of lbm_totals
@@ -145,6 +147,11 @@ struct lbm_ctx {
   char* ws = nullptr;
   Layout lay;
   Slots* slots = nullptr;
+  Slots* shards = nullptr;  // [n_inst][n_shards], or the slots (one shard: small grids, per-cell blending)
+  int n_shards = 1;
+  // whether steps ran since the shards were last folded; a step that the
+  // caller records into a graph may be replayed at any time after (recorded)
+  bool raised = false, recorded = false;
   Inst* insts_dev = nullptr;
   int* items_dev = nullptr;
   hipStream_t stream = nullptr;
@@ -301,6 +308,8 @@ vlbm::StepArgs make_args(const lbm_ctx* c, const void* src, void* dst, int slot)
   a.dst = dst;
   a.plane = c->plane;
   a.slots = c->slots;
+  a.shards = c->shards;
+  a.shard_mask = c->n_shards - 1;
   a.insts = c->insts_dev;
   a.item_inst = c->n_inst > 1 ? c->items_dev : nullptr;
   a.inst0 = c->insts[0];
@@ -355,18 +364,61 @@ lbm_status launch_one(lbm_ctx* c) {
   return LBM_OK;
 }
 
+// Whether work enqueued on the context's stream now is recorded into a graph
+// of the caller's, to run at any time and any number of times without the
+// library's knowledge.
+bool being_recorded(lbm_ctx* c) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->stream, &st) == hipSuccess) return st != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
+
+// Called where steps are enqueued: the shards need a fold before the next
+// read, and before every read once steps were recorded.
+void note_steps(lbm_ctx* c) {
+  c->raised = true;
+  if (!c->recorded) c->recorded = being_recorded(c);
+}
+
+// Folds the shards into the slot records, where steps may have raised them;
+// clear >= 0 also empties that lambda slot.
+hipError_t fold_shards(lbm_ctx* c, int clear) {
+  if (clear < 0 && (c->shards == c->slots || (!c->raised && !c->recorded))) return hipSuccess;
+  if (c->raised && !being_recorded(c)) c->raised = false;
+  return vlbm::launch_fold(c->slots, c->shards, c->n_shards, c->n_inst, clear, c->stream);
+}
+
+// The instances' records with their shards folded in.  A single instance's
+// shards come along in the same copy (they follow its record) and are folded
+// here; an ensemble's are folded on the device first.
 lbm_status read_slots(lbm_ctx* c, std::vector<Slots>& h) {
-  h.resize(c->n_inst);
-  hipError_t e = hipMemcpyAsync(h.data(), c->slots, sizeof(Slots) * c->n_inst,
-                                hipMemcpyDeviceToHost, c->stream);
+  const bool here = c->n_inst == 1 && c->shards != c->slots;
+  const size_t skip = here ? (c->lay.shards - c->lay.slots) / sizeof(Slots) : 0;
+  h.resize(here ? skip + c->n_shards : c->n_inst);
+  hipError_t e = here ? hipSuccess : fold_shards(c, -1);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(h.data(), c->slots, sizeof(Slots) * h.size(), hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reading device slots");
+  if (here) {
+    for (int i = 0; i < c->n_shards; ++i) {
+      const Slots& sh = h[skip + i];
+      // (bit patterns of non-negative doubles order like the integers)
+      for (int k = 0; k < 3; ++k) h[0].lam[k] = std::max(h[0].lam[k], sh.lam[k]);
+      for (int k = 0; k < vlbm::CNT_N; ++k) h[0].cnt[k] += sh.cnt[k];
+    }
+    h.resize(1);
+  }
   return LBM_OK;
 }
 
+// Writes the instances' records back; the shards are empty afterwards.
 lbm_status write_slots(lbm_ctx* c, const std::vector<Slots>& h) {
-  hipError_t e = hipMemcpyAsync(c->slots, h.data(), sizeof(Slots) * c->n_inst,
-                                hipMemcpyHostToDevice, c->stream);
+  std::vector<Slots> all(h);
+  if (c->n_inst == 1 && c->shards != c->slots)
+    all.resize((c->lay.shards - c->lay.slots) / sizeof(Slots) + c->n_shards, Slots{});
+  hipError_t e = hipMemcpyAsync(c->slots, all.data(), sizeof(Slots) * all.size(), hipMemcpyHostToDevice, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "writing device slots");
   return LBM_OK;
@@ -408,6 +460,10 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
   c->lay = layout(p, n, nx, ny);
   c->ws = (char*)ws;
   c->slots = (Slots*)(c->ws + c->lay.slots);
+  long long strips = 0;
+  for (int i = 0; i < n; ++i) strips += strips_x(nx[i]) * strips_y(ny[i], kMinStripRows);
+  c->n_shards = p->blend == LBM_BLEND_FACE ? vlbm::shards_for(strips / n) : 1;
+  c->shards = c->n_shards > 1 ? (Slots*)(c->ws + c->lay.shards) : c->slots;
   c->insts_dev = (Inst*)(c->ws + c->lay.insts);
   c->items_dev = (int*)(c->ws + c->lay.items);
   c->insts.resize(n);
@@ -439,8 +495,9 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
     delete c;
     return st;
   }
+  // the records and, behind them, their shards
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)c->slots, 0u,
-                                       (long long)(sizeof(Slots) * n / 4), c->stream);
+                                       (long long)((c->lay.slots_save - c->lay.slots) / 4), c->stream);
   if (e == hipSuccess)
     e = vlbm::launch_init(c->sc, c->insts.data(), n, c->insts_dev, c->plane, u0, c->cur(),
                           c->slots, p->precision, c->blocked, c->stream);
@@ -503,6 +560,7 @@ lbm_status lbm_init_batch(const lbm_params* p, int32_t n, const int32_t* nx, con
 lbm_status lbm_step(lbm_ctx* c, int32_t nsteps) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (nsteps < 0) return fail(c, LBM_EINVAL, "nsteps must be >= 0");
+  note_steps(c);
   for (int32_t k = 0; k < nsteps; ++k) {
     lbm_status s = launch_one(c);
     if (s != LBM_OK) return s;
@@ -569,6 +627,7 @@ lbm_status lbm_step_graph(lbm_ctx* c, int32_t nsteps) {
   // a graph captured before lbm_step_between would step the context's own,
   // stale buffers
   if (lbm_status st = require_attached(c)) return st;
+  note_steps(c);
   while (nsteps > 0) {
     const int32_t k = nsteps > kGraphChunk ? kGraphChunk : nsteps;
     const lbm_status st = replay_graph(c, k);
@@ -586,6 +645,7 @@ lbm_status lbm_step_theta(lbm_ctx* c, double* tx, double* ty) {
   vlbm::StepArgs a = make_args(c, c->cur(), c->other(), (int)(c->step % 3));
   a.theta_x = tx;
   a.theta_y = ty;
+  note_steps(c);
   hipError_t e = launch_step_with_bnd(c, a);
   if (e != hipSuccess) return hip_fail(c, e, "step launch");
   c->step += 1;
@@ -751,8 +811,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
                                              c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "set_state copy");
   const int slot = (int)(c->step % 3);
-  for (int i = 0; i < c->n_inst && e == hipSuccess; ++i)
-    e = vlbm::launch_fill_u32((unsigned int*)&c->slots[i].lam[slot], 0u, 2, c->stream);
+  if (e == hipSuccess) e = fold_shards(c, slot);
   if (e == hipSuccess)
     e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->n_inst, c->plane, c->cur(),
                                   c->slots, slot, c->p.precision, c->blocked, c->stream);
@@ -776,6 +835,7 @@ lbm_status lbm_step_between(lbm_ctx* c, const void* src, void* dst, double* tx, 
   vlbm::StepArgs a = make_args(c, src, dst, (int)(c->step % 3));
   a.theta_x = tx;
   a.theta_y = ty;
+  note_steps(c);
   hipError_t e = launch_step_with_bnd(c, a);
   if (e != hipSuccess) return hip_fail(c, e, "step launch");
   c->step += 1;
@@ -1057,6 +1117,12 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  if (c->n_inst > 1) {
+    // (the fold empties the shards that the timed launches raised)
+    c->raised = true;
+    const hipError_t e = fold_shards(c, -1);
+    if (e != hipSuccess) return hip_fail(c, e, "autotune");
+  }
   st = write_slots(c, saved);
   if (st != LBM_OK) return st;
   c->strip_mode = best_m;
@@ -1184,6 +1250,8 @@ extern "C" lbm_status lbm_step_adjoint(lbm_ctx* c, const double* U, const double
   e = hipMemcpyAsync(save, c->slots, sizeof(Slots), hipMemcpyDeviceToDevice, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "adjoint slot save");
   vlbm::StepArgs a = make_args(c, U, c->other(), scratch);
+  a.shards = c->slots;  // the parked record alone
+  a.shard_mask = 0;
   a.theta_x = tx;
   a.theta_y = ty;
   // (lambda^n raised by the Dirichlet states first, as in the forward step)

@@ -21,10 +21,10 @@ using vlbm::Slots;
 
 namespace {
 
-// One 128-byte record of per-step scalars (vlbm::Slots) at the start; the
-// rest is padding to the stated size.
+// One 128-byte record of per-step scalars (vlbm::Slots) at the start, then its
+// shards.
 constexpr size_t kScratchBytes = LBM_NOALLOC_SCRATCH_BYTES;
-static_assert(sizeof(Slots) <= kScratchBytes, "the scalar record fits the scratch array");
+static_assert(sizeof(Slots) * (1 + vlbm::kShards) <= kScratchBytes, "the record and its shards fit the scratch array");
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
@@ -106,7 +106,7 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   // zero the record, lambda^n of src into slot 0, then clear the counters
   // that the reduction raised for non-admissible cells of src (they count
   // the step's output cells only, as in a context)
-  hipError_t e = vlbm::launch_fill_u32((unsigned int*)sl, 0u, (long long)(sizeof(Slots) / 4), s);
+  hipError_t e = vlbm::launch_fill_u32((unsigned int*)sl, 0u, (long long)(kScratchBytes / 4), s);
   if (e == hipSuccess) e = vlbm::launch_lambda_state(sc, &in, 1, cells, src_dev, sl, 0, p->precision, 0, s);
   if (e == hipSuccess)
     e = vlbm::launch_fill_u32((unsigned int*)((char*)base + offsetof(Slots, cnt)), 0u,
@@ -119,6 +119,9 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   a.dst = dst_dev;
   a.plane = cells;
   a.slots = sl;
+  const int n_shards = vlbm::shards_for((long long)in.xs * ((p->ny + 3) / 4));
+  a.shards = n_shards > 1 ? sl + 1 : sl;
+  a.shard_mask = n_shards - 1;
   a.insts = nullptr;
   a.item_inst = nullptr;
   a.inst0 = in;
@@ -135,7 +138,8 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   if (!diag_host) return LBM_OK;
 
   Slots h;
-  e = hipMemcpyAsync(&h, base, sizeof(Slots), hipMemcpyDeviceToHost, s);
+  e = vlbm::launch_fold(sl, a.shards, n_shards, 1, -1, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(&h, base, sizeof(Slots), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "lbm_step_noalloc: reading the step's scalars failed");
   double lam;

@@ -44,6 +44,7 @@
 #include <math.h>
 
 #include <atomic>
+#include <type_traits>
 
 #include "vlbm_internal.h"
 
@@ -266,13 +267,60 @@ __device__ __forceinline__ void raise_lambda(unsigned long long* p, double lmax)
   if (v > seen) atomicMax(p, v);
 }
 
+// Largest value over the wave, through DPP row shifts and broadcasts (lane 63
+// ends up with all 64; lanes without a source keep their own value).
+__device__ __forceinline__ double wave_max(double v) {
+  auto step = [&](auto ctrl) {
+    const long long b = __double_as_longlong(v);
+    const int lo = (int)(b & 0xffffffffll), hi = (int)(b >> 32);
+    const int slo = __builtin_amdgcn_update_dpp(lo, lo, decltype(ctrl)::value, 0xf, 0xf, false);
+    const int shi = __builtin_amdgcn_update_dpp(hi, hi, decltype(ctrl)::value, 0xf, 0xf, false);
+    v = vmax(v, __longlong_as_double(((long long)shi << 32) | (unsigned int)slo));
+  };
+  step(std::integral_constant<int, 0x111>{});  // row_shr:1
+  step(std::integral_constant<int, 0x112>{});  // row_shr:2
+  step(std::integral_constant<int, 0x114>{});  // row_shr:4
+  step(std::integral_constant<int, 0x118>{});  // row_shr:8
+  step(std::integral_constant<int, 0x142>{});  // row_bcast:15
+  step(std::integral_constant<int, 0x143>{});  // row_bcast:31
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), 63);
+  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), 63);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+
+// The records that the waves of instance ii raise (see Slots): record `k & mask`.
+__device__ __forceinline__ Slots* shard_of(const StepArgs& A, int ii, long long k) {
+  return A.shards + ((long long)ii * (A.shard_mask + 1) + (int)(k & A.shard_mask));
+}
+
+// lambda^n of instance ii: the largest of the slot's own value (initialisation,
+// set_state and Dirichlet states raise that one) and of the shards'.
+__device__ __forceinline__ double step_lambda(const StepArgs& A, int ii, int lane) {
+  const double own = __longlong_as_double((long long)A.slots[ii].lam[A.slot]);
+  if (A.shard_mask == 0) return own;  // the slots themselves
+  return vmax(own, wave_max(__longlong_as_double((long long)shard_of(A, ii, lane)->lam[A.slot])));
+}
+
+// The bookkeeping of a step, by the wave of the instance's first strip: the
+// lambda slot after the next is cleared, the time advances.
+__device__ __forceinline__ void begin_step(const StepArgs& A, int ii, double dx, double a, double lam, int lane) {
+  Slots* sl = A.slots + ii;
+  if (lane <= A.shard_mask) shard_of(A, ii, lane)->lam[(A.slot + 2) % 3] = 0ull;
+  if (lane == 0) {
+    sl->lam[(A.slot + 2) % 3] = 0ull;
+    sl->t[(A.slot + 1) % 3] = sl->t[A.slot] + dx / a;
+    if (A.sc.a_mode == 1 && a < 2.0 * lam / (1.0 - A.sc.alpha)) atomicOr(&sl->cnt[CNT_BOUCHUT], 1ull);
+  }
+}
+
 // One lane per wave publishes the wave's wavespeed maximum and event counts;
 // n_cls packs the non-finite count (bits 16 and up) and the rho <= 0 count
 // (low 16 bits) of the non-admissible cells.
 __device__ __forceinline__ void publish(Slots* sl, int slot, double lmax, unsigned n_bad,
                                        unsigned n_guard, unsigned n_lim, unsigned n_lmp,
                                        unsigned n_nf, unsigned n_rho) {
-  raise_lambda(&sl->lam[slot], lmax);
+  if (lmax > 0.0) raise_lambda(&sl->lam[slot], lmax);
   if (n_bad) atomicAdd(&sl->cnt[CNT_BAD], (unsigned long long)n_bad);
   if (n_nf) atomicAdd(&sl->cnt[CNT_NONFINITE], (unsigned long long)n_nf);
   if (n_rho) atomicAdd(&sl->cnt[CNT_RHO], (unsigned long long)n_rho);
@@ -463,7 +511,7 @@ __device__ void bnd_cell(const StepArgs& A, const BndDesc& bd, const Inst& in, c
 // with the same inputs and code, so both cells of a strip-edge face see the
 // same theta.
 template <class T, class C, int LIMS, bool TH, bool BND>
-__device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, Slots* sl, int xs,
+__device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                             int ys, int lane) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -479,14 +527,10 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, S
   const int y1 = min(y0 + in.strip_h, ny);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
-  const double lam = __longlong_as_double((long long)sl->lam[A.slot]);
+  const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
 
-  if (xs == 0 && ys == 0 && lane == 0) {
-    sl->lam[(A.slot + 2) % 3] = 0ull;
-    sl->t[(A.slot + 1) % 3] = sl->t[A.slot] + in.dx / K.a;
-    if (sc.a_mode == 1 && K.a < 2.0 * lam / (1.0 - sc.alpha)) atomicOr(&sl->cnt[CNT_BOUCHUT], 1ull);
-  }
+  if (xs == 0 && ys == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
 
   // plane q of this instance starts at base + q P; a cell is addressed by a
   // 32-bit offset row * nx + column from that uniform base
@@ -505,7 +549,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, S
   // with boundary descriptions, ghost rows, columns past the edge and the
   // halo columns come from bnd_cell
   BndDesc bd{};
-  if constexpr (BND) bd = bnd_desc(A, sl);
+  if constexpr (BND) bd = bnd_desc(A, A.slots + ii);
   auto bnd_load = [&](const int R) {
     if (R < 0 || R >= ny || !lane_out) {
       bnd_cell<T, C>(A, bd, in, sbase, P, gi < nx + 1 ? gi : nx + 1, R, K, raw);
@@ -714,7 +758,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, S
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(sl, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
 }
 
 // One aligned strip of the bounds-limited scheme (LMP / RLMP, eq. (29)):
@@ -728,7 +772,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, S
 // and lane 0 the west edge face x0 - 1/2, with the same expressions as every
 // other lane, so both strips beside an edge face see the same theta.
 template <class T, class C, int LIMS, bool TH, bool BND>
-__device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, Slots* sl, int xs,
+__device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                           int ys, int lane) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -744,14 +788,10 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, Slo
   const int y1 = min(y0 + in.strip_h, ny);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
-  const double lam = __longlong_as_double((long long)sl->lam[A.slot]);
+  const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
 
-  if (xs == 0 && ys == 0 && lane == 0) {
-    sl->lam[(A.slot + 2) % 3] = 0ull;
-    sl->t[(A.slot + 1) % 3] = sl->t[A.slot] + in.dx / K.a;
-    if (sc.a_mode == 1 && K.a < 2.0 * lam / (1.0 - sc.alpha)) atomicOr(&sl->cnt[CNT_BOUCHUT], 1ull);
-  }
+  if (xs == 0 && ys == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
 
   const T* __restrict__ sbase = (const T*)A.src + in.off;
   T* __restrict__ dbase = (T*)A.dst + in.off;
@@ -802,7 +842,7 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, Slo
   // with boundary descriptions, ghost rows, columns past the edge and the
   // halo columns come from bnd_cell
   BndDesc bd{};
-  if constexpr (BND) bd = bnd_desc(A, sl);
+  if constexpr (BND) bd = bnd_desc(A, A.slots + ii);
   auto bnd_load = [&](const int R) {
     if (R < 0 || R >= ny || !lane_out) {
       bnd_cell<T, C>(A, bd, in, sbase, P, gi < nx + 1 ? gi : nx + 1, R, K, raw);
@@ -1087,7 +1127,7 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, Slo
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(sl, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
 }
 
 // ------------------------------------------ bounds-limited march, LDS-staged
@@ -1117,7 +1157,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // The loads into LDS are not tracked by the compiler's wait counters:
 // the march waits on the vector-memory counter itself (see the loop head).
 template <class T, class C, int LIMS, bool TH, bool BLK>
-__device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in, Slots* sl, int xs,
+__device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                               int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -1127,15 +1167,11 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
   const int y0 = ys * in.strip_h;
   const int y1 = min(y0 + in.strip_h, ny);
 
-  const double lam = __longlong_as_double((long long)sl->lam[A.slot]);
+  const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
-  if (xs == 0 && ys == 0 && lane == 0) {
-    sl->lam[(A.slot + 2) % 3] = 0ull;
-    sl->t[(A.slot + 1) % 3] = sl->t[A.slot] + in.dx / K.a;
-    if (sc.a_mode == 1 && K.a < 2.0 * lam / (1.0 - sc.alpha)) atomicOr(&sl->cnt[CNT_BOUCHUT], 1ull);
-  }
+  if (xs == 0 && ys == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
 
   // the instance's first value: planar, cell (0, 0) of plane 0; blocked,
   // its whole state follows the instances before it
@@ -1443,7 +1479,7 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(sl, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
 }
 
 // ------------------------------------------ short march, LDS-staged
@@ -1455,7 +1491,7 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
 // boundary descriptions), where a strip row is one contiguous range; planar
 // states take march_short.
 template <class T, class C, int LIMS, bool TH, bool BLK>
-__device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& in, Slots* sl, int xs,
+__device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                                 int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -1466,14 +1502,10 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
   const int y1 = min(y0 + in.strip_h, ny);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
-  const double lam = __longlong_as_double((long long)sl->lam[A.slot]);
+  const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
 
-  if (xs == 0 && ys == 0 && lane == 0) {
-    sl->lam[(A.slot + 2) % 3] = 0ull;
-    sl->t[(A.slot + 1) % 3] = sl->t[A.slot] + in.dx / K.a;
-    if (sc.a_mode == 1 && K.a < 2.0 * lam / (1.0 - sc.alpha)) atomicOr(&sl->cnt[CNT_BOUCHUT], 1ull);
-  }
+  if (xs == 0 && ys == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
 
   // the instance's first value: planar, cell (0, 0) of plane 0; blocked,
   // its whole state follows the instances before it
@@ -1684,7 +1716,7 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(sl, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
 }
 
 // The step kernel: T the state's storage type, C its arithmetic type, LMP the
@@ -1722,13 +1754,13 @@ void step_kernel(StepArgs A) {
     const int xs = (int)(local % in.xs);
     const int ys = (int)(local / in.xs);
     if constexpr (LMP && DMA)
-      march_lmp_dma<T, C, LIMS, TH, BLK>(A, in, A.slots + ii, xs, ys, lane, wave);
+      march_lmp_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
     else if constexpr (LMP)
-      march_lmp<T, C, LIMS, TH, BND>(A, in, A.slots + ii, xs, ys, lane);
+      march_lmp<T, C, LIMS, TH, BND>(A, in, ii, item, xs, ys, lane);
     else if constexpr (DMA)
-      march_short_dma<T, C, LIMS, TH, BLK>(A, in, A.slots + ii, xs, ys, lane, wave);
+      march_short_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
     else
-      march_short<T, C, LIMS, TH, BND>(A, in, A.slots + ii, xs, ys, lane);
+      march_short<T, C, LIMS, TH, BND>(A, in, ii, item, xs, ys, lane);
   }
 }
 
@@ -2092,6 +2124,31 @@ __global__ __launch_bounds__(256) void relayout_kernel(const T* __restrict__ src
   }
 }
 
+// Folds each instance's shards into its slot record (lambda: the largest,
+// counters: the sum) and clears them; one wave per instance.  clear >= 0 also
+// empties that lambda slot afterwards (a new state's wavespeed goes there).
+__global__ __launch_bounds__(64) void fold_kernel(Slots* slots, Slots* shards, int n_shards, int clear) {
+  Slots* sl = slots + blockIdx.x;
+  Slots* sh = shards + (long long)blockIdx.x * n_shards;
+  const int lane = threadIdx.x;
+  const bool has = lane < n_shards && sh != sl;  // (a context without shards of its own uses the record)
+  for (int k = 0; k < 3; ++k) {
+    const double m = wave_max(has ? __longlong_as_double((long long)sh[lane].lam[k]) : 0.0);
+    if (has) sh[lane].lam[k] = 0ull;
+    if (lane == 0) {
+      const double own = __longlong_as_double((long long)sl->lam[k]);
+      sl->lam[k] = k == clear ? 0ull : (unsigned long long)__double_as_longlong(vmax(own, m));
+    }
+  }
+  for (int k = 0; k < CNT_N; ++k) {
+    unsigned long long n = has ? sh[lane].cnt[k] : 0ull;
+    if (has) sh[lane].cnt[k] = 0ull;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) n += __shfl_xor(n, off, 64);
+    if (lane == 0 && n) sl->cnt[k] += n;
+  }
+}
+
 __global__ void fill_u32_kernel(unsigned int* p, unsigned int v, long long n) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -2363,6 +2420,11 @@ hipError_t launch_minima(const Inst& in, long long plane, const void* S, double*
   else
     hipLaunchKernelGGL((minima_kernel<float>), dim3(blocks), dim3(256), 0, s,
                        (const float*)S + in.off * (blocked ? 20 : 1), plane, n, part, blocked);
+  return hipGetLastError();
+}
+
+hipError_t launch_fold(Slots* slots, Slots* shards, int n_shards, int n_inst, int clear, hipStream_t s) {
+  hipLaunchKernelGGL(fold_kernel, dim3((unsigned)n_inst), dim3(64), 0, s, slots, shards, n_shards, clear);
   return hipGetLastError();
 }
 

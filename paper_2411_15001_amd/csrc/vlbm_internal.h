@@ -54,11 +54,35 @@ enum {
 };
 static_assert(sizeof(Slots) == 128, "one 128-byte record per instance");
 
+// Shards: the step kernels raise lambda and the counters of an instance in
+// kShards further records of the same form (t unused).  Atomics of many waves
+// on one cache line queue at 40-100 ns each (the L2s of the XCDs are not
+// shared, so they meet at the memory side): with one record the last waves of a
+// short launch waited for the others' counts, 53 us a step on a 400^2 grid
+// under LMP, where most waves hold a limited face, against 38 us with the
+// records spread; 293 against 276 us at 2048^2.  8 records: 40 us, 16: 38.4,
+// 32 and 64: 38.0.  The next step takes the largest of the shards' lambdas;
+// launch_fold folds the shards into the instance's own record before the host
+// reads that.
+constexpr int kShards = 32;  // at most the wave's 64 lanes, a power of two
+// Shards in use for an instance of `strips` strips of four rows (fixed for a
+// context): one for every 16 strips; a single one is the slot record itself.  On the smallest grids, whose few waves
+// do not queue, reading 32 lines instead of one at the start of every step
+// costs more than it saves (64^2: 0.8 us of 17).
+inline int shards_for(long long strips) {
+  int n = 1;
+  while (n < kShards && n * 16 < strips) n *= 2;
+  return n;
+}
+
 struct StepArgs {
   const void* src;
   void* dst;
   long long plane;        // elements per plane (sum of all instances' cells)
   Slots* slots;           // [n_inst]
+  Slots* shards;          // [n_inst][shard_mask + 1]; the slots themselves (mask 0) where
+                          // the launch's records are parked or there are no others
+  int shard_mask;
   const Inst* insts;      // [n_inst], device memory
   const int* item_inst;   // [n_items] instance of every item (batches), or null
   Inst inst0;             // the instance when n_inst == 1
@@ -113,6 +137,7 @@ hipError_t launch_minima(const Inst& in, long long plane, const void* S, double*
 // grid is `blocks` workgroups of 256 threads.
 hipError_t launch_totals(const Inst& in, long long plane, const void* S, double* part,
                          int blocks, int precision, int blocked, hipStream_t s);
+hipError_t launch_fold(Slots* slots, Slots* shards, int n_shards, int n_inst, int clear, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStream_t s);
 // Raises each instance's lam[slot] to the largest wavespeed of its Dirichlet
 // boundary states (one workgroup per instance).
