@@ -159,6 +159,8 @@ struct lbm_ctx {
   long long step = 0;
   int strip_rows = 64;
   int strip_mode = 0;  // 0: every instance strip_rows; 1: matched to the instance's height
+  bool manual = false;  // the launch shape was given by the caller or the tuner
+  int rows = 0;         // steps run the row kernel (see use_rows)
   int waves = 4;
   int xcd = 1;
   int grid_per_cu = 0;  // 0: one wave per strip; k > 0: persistent grid of k groups per CU
@@ -205,6 +207,7 @@ lbm_status hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
 // least kMinStripRows), so that small instances are cut into more, shorter
 // strips while large ones keep tall strips and few re-read halo rows.
 int inst_strip_rows(const lbm_ctx* c, int ny) {
+  if (c->rows) return vlbm::kRowsPerGroup;
   if (c->strip_mode == 0) return c->strip_rows;
   int h = kMinStripRows;
   while (h * 2 <= c->strip_rows && h * 2 <= ny / 4) h *= 2;
@@ -219,6 +222,13 @@ lbm_status require_attached(lbm_ctx* c) {
   return LBM_OK;
 }
 
+// Whether the default launch of a context is the row kernel's.
+bool default_rows(const lbm_ctx* c) {
+  long long strip_rows = 0;
+  for (const Inst& in : c->insts) strip_rows += strips_x(in.nx) * in.ny;
+  return vlbm::use_rows(strip_rows, c->n_inst, c->has_bnd, c->p.precision, c->sc);
+}
+
 // Rebuild the strip tables after a change of strip height.  Each instance's
 // strips are consecutive work items; in mode 1 the instances with the tallest
 // strips (and, among equal heights, the most rows) come first, so that the
@@ -226,6 +236,7 @@ lbm_status require_attached(lbm_ctx* c) {
 // launch.
 void build_items(lbm_ctx* c) {
   std::vector<int> order(c->n_inst);
+  c->rows = !c->manual && default_rows(c) ? 1 : 0;
   for (int i = 0; i < c->n_inst; ++i) {
     order[i] = i;
     Inst& in = c->insts[i];
@@ -288,6 +299,16 @@ lbm_status rebuild_launch(lbm_ctx* c) {
   return upload_tables(c);
 }
 
+// Back to the launch of a new context.
+lbm_status default_launch(lbm_ctx* c) {
+  c->manual = false;
+  c->strip_rows = default_strip_rows(c);
+  c->strip_mode = 0;
+  c->waves = 4;
+  c->grid_per_cu = 0;
+  return rebuild_launch(c);
+}
+
 // Workgroups of a step launch.  By default one wave per strip, for single
 // instances and ensembles alike; with grid_per_cu = k > 0 a persistent grid
 // of k workgroups per compute unit whose waves stride over the strips (the
@@ -295,6 +316,7 @@ lbm_status rebuild_launch(lbm_ctx* c) {
 // 256-instance ensemble the persistent grid measured 1-4% slower; the
 // autotuner times both.
 int compute_groups(const lbm_ctx* c) {
+  if (c->rows) return (int)((c->n_items + 7) / 8 * 8);
   long long g = (c->n_items + c->waves - 1) / c->waves;
   if (c->grid_per_cu > 0) g = std::min(g, (long long)c->grid_per_cu * c->n_cu);
   if (c->xcd) g = (g + 7) / 8 * 8;
@@ -319,6 +341,7 @@ vlbm::StepArgs make_args(const lbm_ctx* c, const void* src, void* dst, int slot)
   a.waves_per_group = c->waves;
   a.xcd_remap = c->xcd;
   a.groups = compute_groups(c);
+  a.rows = c->rows;
   a.sc = c->sc;
   if (c->n_inst > 1)
     a.bnd_table = (const vlbm::BndDesc*)(c->ws + c->lay.bndt);
@@ -853,6 +876,7 @@ lbm_status lbm_set_launch(lbm_ctx* c, int32_t rows, int32_t waves) {
   if (waves != 0 && (waves < 1 || waves > 4)) return fail(c, LBM_EINVAL, "waves per group must lie in [1, 4]");
   if (rows) c->strip_rows = rows;
   if (waves) c->waves = waves;
+  if (rows || waves) c->manual = true;
   return rebuild_launch(c);
 }
 
@@ -860,6 +884,7 @@ lbm_status lbm_set_strip_mode(lbm_ctx* c, int32_t mode) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (mode != 0 && mode != 1) return fail(c, LBM_EINVAL, "strip mode must be 0 or 1");
   c->strip_mode = mode;
+  if (mode) c->manual = true;
   return rebuild_launch(c);
 }
 
@@ -918,8 +943,7 @@ lbm_status lbm_set_instance_boundary(lbm_ctx* c, int32_t inst, int32_t side, con
       c->has_bnd |= c->bnd[i].kind[k] != nullptr;
       c->has_dirichlet |= c->side_dirichlet[i][k];
     }
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
+  if (lbm_status st = rebuild_launch(c)) return st;
   if (c->blocked && c->has_bnd) {
     // the kernels that read descriptions take the planar layout: convert the
     // current state once, through the other buffer (which the next step
@@ -965,9 +989,8 @@ lbm_status lbm_set_grid(lbm_ctx* c, int32_t groups_per_cu) {
   if (groups_per_cu < 0 || groups_per_cu > kMaxGridPerCu)
     return fail(c, LBM_EINVAL, "groups per compute unit must lie in [0, 32]");
   c->grid_per_cu = groups_per_cu;
-  for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
-  c->graphs.clear();
-  return LBM_OK;
+  if (groups_per_cu) c->manual = true;
+  return rebuild_launch(c);
 }
 
 lbm_status lbm_get_grid(const lbm_ctx* c, int32_t* groups_per_cu, int32_t* groups) {
@@ -1010,6 +1033,7 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
         int rows = 0, waves = 0, grid = 0, mode = 0;
         const int got = sscanf(text.c_str() + pos + k.size(), " : [ %d , %d , %d , %d ]", &rows, &waves,
                                &grid, &mode);
+        if (got >= 2 && rows == 0) return default_launch(c);
         if (got >= 2) {
           lbm_status st = lbm_set_launch(c, rows, waves);
           if (st == LBM_OK) st = lbm_set_grid(c, got >= 3 ? grid : 0);
@@ -1035,9 +1059,14 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
   // read the current state and write the other buffer, so the state is not
   // advanced
   auto time_shape = [&](int r, int w, int gpc, int mode, float work_ms, float& ms) -> lbm_status {
-    c->strip_mode = mode;
-    lbm_status s2 = lbm_set_launch(c, r, w);
-    if (s2 == LBM_OK) s2 = lbm_set_grid(c, gpc);
+    lbm_status s2;
+    if (r == 0) {
+      s2 = default_launch(c);
+    } else {
+      c->strip_mode = mode;
+      s2 = lbm_set_launch(c, r, w);
+      if (s2 == LBM_OK) s2 = lbm_set_grid(c, gpc);
+    }
     if (s2 != LBM_OK) return s2;
     ms = -1.0f;
     // a persistent grid no smaller than one wave per strip is the same launch
@@ -1077,6 +1106,12 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
     (void)hipEventDestroy(e1);
     return s2;
   };
+  if (default_rows(c)) {  // the row kernel (recorded as rows = 0)
+    float ms = -1.0f;
+    st = time_shape(0, 0, 0, 0, 4.0f, ms);
+    if (st != LBM_OK) return bail(st);
+    cands.push_back({ms, 0, 0, 0, 0, {0.0f, 0.0f, 0.0f}});
+  }
   int max_ny = 0;
   for (const Inst& in : c->insts) max_ny = std::max(max_ny, in.ny);
   for (int r : rows_c) {
@@ -1125,9 +1160,13 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
   }
   st = write_slots(c, saved);
   if (st != LBM_OK) return st;
-  c->strip_mode = best_m;
-  st = lbm_set_launch(c, best_r, best_w);
-  if (st == LBM_OK) st = lbm_set_grid(c, best_g);
+  if (best_r == 0) {
+    st = default_launch(c);
+  } else {
+    c->strip_mode = best_m;
+    st = lbm_set_launch(c, best_r, best_w);
+    if (st == LBM_OK) st = lbm_set_grid(c, best_g);
+  }
   if (st != LBM_OK) return st;
   if (path) {
     // append the entry to the flat JSON object

@@ -99,8 +99,9 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   in.dx = p->dx;
   in.nx = p->nx;
   in.ny = p->ny;
-  in.strip_h = strip_rows(p->nx, p->ny, p->precision);
   in.xs = (p->nx + 63) / 64;
+  const int rows = vlbm::use_rows((long long)in.xs * p->ny, 1, false, p->precision, sc) ? 1 : 0;
+  in.strip_h = rows ? vlbm::kRowsPerGroup : strip_rows(p->nx, p->ny, p->precision);
   in.ys = (p->ny + in.strip_h - 1) / in.strip_h;
 
   // zero the record, lambda^n of src into slot 0, then clear the counters
@@ -130,7 +131,8 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   a.slot = 0;
   a.waves_per_group = 4;
   a.xcd_remap = 1;
-  a.groups = (int)(((a.n_items + 3) / 4 + 7) / 8 * 8);
+  a.rows = rows;
+  a.groups = (int)(((rows ? a.n_items : (a.n_items + 3) / 4) + 7) / 8 * 8);
   a.sc = sc;
   a.bnd = 0;
   e = vlbm::launch_step(a, p->precision, s);

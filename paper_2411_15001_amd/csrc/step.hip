@@ -289,6 +289,8 @@ __device__ __forceinline__ double wave_max(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+__device__ __forceinline__ unsigned wave_count(bool b) { return (unsigned)__popcll(__ballot(b)); }
+
 // The records that the waves of instance ii raise (see Slots): record `k & mask`.
 __device__ __forceinline__ Slots* shard_of(const StepArgs& A, int ii, long long k) {
   return A.shards + ((long long)ii * (A.shard_mask + 1) + (int)(k & A.shard_mask));
@@ -420,6 +422,31 @@ __device__ __forceinline__ StepConst<T, C> step_const(const Scheme& s, double la
   k.alpha = (C)s.alpha;
   k.gm1 = (C)(s.gamma - 1.0);
   return k;
+}
+
+// The same constants in scalar registers (they are equal in every lane).
+__device__ __forceinline__ double uniform(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_readfirstlane((int)(b & 0xffffffffll));
+  const int hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ float uniform(float v) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(v)));
+}
+template <class T, class C>
+__device__ __forceinline__ StepConst<T, C> uniform_const(const StepConst<T, C>& k) {
+  StepConst<T, C> u;
+  u.lam = uniform(k.lam);
+  u.a = uniform(k.a);
+  u.kappa = uniform(k.kappa);
+  u.w = uniform(k.w);
+  u.r2a = uniform(k.r2a);
+  u.r2k = uniform(k.r2k);
+  u.ac = uniform(k.ac);
+  u.alpha = uniform(k.alpha);
+  u.gm1 = uniform(k.gm1);
+  return u;
 }
 
 // Boundary cells with a kind per cell (reflective wall, Dirichlet state,
@@ -1719,6 +1746,383 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
   if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
 }
 
+// ------------------------------------------------------------- one row per wave
+
+// One row of one strip: the 64 cells x0 .. x0 + 63 of row j, with everything
+// they read loaded at once: the row itself, u and u_3 of the row below, u and
+// u_4 of the row above, and with density bounds rho and m_2 of the rows two
+// away (a cell's bounds need the densities of its four face states).  Both
+// y-faces are evaluated here, so a face between two rows is evaluated twice,
+// with the same expressions and inputs.  Values, evaluation order and results
+// are those of the marches.
+//
+// For grids that give the marches too few or too short strips (use_rows): a
+// march is a chain of rows, 2.4-4 us each with one wave per SIMD, six rows at
+// the least; here the chain is one row, and with 164 (float64; 192 under
+// density bounds) or 114 registers two to four waves share a SIMD.  What
+// bounds it: at 64^2 a wave lives 7 us, of which 3 wait for the first loads and
+// the kernel's code and 2 issue its 1035 vector instructions; at 512^2
+// (float64, PP, 4 rows per SIMD, 3 resident) 20 us a step, 7.3 of them vector issue.
+struct RowEvents {
+  double lmax;
+  unsigned n[6];  // bad, non-finite, rho <= 0, guard, limited, lmp
+};
+
+template <class T, class C, bool LMP, int LIMS, bool TH, bool BND, bool BLK>
+__device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in, int ii, int xs, int j, int lane,
+                                              const Slots* shard) {
+  const Scheme& sc = A.sc;
+  const int nx = in.nx, ny = in.ny;
+  const int x0 = xs * 64;
+  const int gi = x0 + lane;
+  const bool lane_out = gi < nx;
+  const bool first = lane == 0, last = lane == 63;
+  const bool sponge = LIMS == 0 && sc.sponge > 0;
+  const double lam = step_lambda(A, ii, lane);
+
+  const T* __restrict__ sbase = (const T*)A.src + in.off * (BLK ? 20 : 1);
+  T* __restrict__ dbase = (T*)A.dst + in.off * (BLK ? 20 : 1);
+  const long long P = A.plane;
+  // value q of the cell in column c of the row that starts at element r
+  // (row * nx; blocked: of the row's first 64-cell run, and a run holds 1280)
+  auto at = [&](int q, long long r, int c) -> T {
+    if constexpr (BLK)
+      return sbase[r * 20 + (long long)(c >> 6) * 1280 + q * 64 + (c & 63)];
+    else
+      return (sbase + q * P)[(unsigned)r + (unsigned)c];
+  };
+
+  // rows j - 2 .. j + 2 of the lane's column, and of the halo column x0 - 1
+  // (lane 0) or x0 + 64 (lane 63); the outer column x0 - 2 or x0 + 65
+  T own[20], south[8], north[8], south2[2], north2[2];
+  T halo[8] = {}, hsouth[3] = {}, hnorth[3] = {}, outer[2] = {};
+  StepConst<T, C> K;
+  if constexpr (BND) K = step_const<T, C>(sc, lam);
+  bool plain = true;
+  if constexpr (BND) {
+    // interior rows and strips read no ghost
+    plain = j >= 2 && j + 2 < ny && x0 >= 2 && x0 + 66 <= nx;
+    if (!plain) {
+      const BndDesc bd = bnd_desc(A, A.slots + ii);
+#pragma unroll 1
+      for (int dr = LMP ? -2 : -1; dr <= (LMP ? 2 : 1); ++dr) {
+        T t[20];
+        bnd_cell<T, C>(A, bd, in, sbase, P, min(gi, nx + 1), j + dr, K, t);
+        if (dr == 0) {
+#pragma unroll
+          for (int q = 0; q < 20; ++q) own[q] = t[q];
+        } else if (dr == -1) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            south[q] = t[q];
+            south[4 + q] = t[12 + q];
+          }
+        } else if (dr == 1) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            north[q] = t[q];
+            north[4 + q] = t[16 + q];
+          }
+        } else if (dr == -2) {
+          south2[0] = t[0];
+          south2[1] = t[2];
+        } else {
+          north2[0] = t[0];
+          north2[1] = t[2];
+        }
+      }
+      if (first || last) {
+#pragma unroll 1
+        for (int k = LMP ? 0 : 1; k < (LMP ? 4 : 2); ++k) {
+          // the halo cell of rows j - 1, j, j + 1 and the outer cell of row j
+          const int c = first ? (k == 3 ? x0 - 2 : x0 - 1) : min(k == 3 ? x0 + 65 : x0 + 64, nx + 1);
+          T t[20];
+          bnd_cell<T, C>(A, bd, in, sbase, P, c, k == 3 ? j : j + k - 1, K, t);
+          if (k == 1) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              halo[q] = t[q];
+              halo[4 + q] = first ? t[4 + q] : t[8 + q];
+            }
+          } else if (k == 0) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) hsouth[q] = t[q];
+          } else if (k == 2) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) hnorth[q] = t[q];
+          } else {
+            outer[0] = t[0];
+            outer[1] = t[1];
+          }
+        }
+      }
+    }
+  }
+  if (plain) {
+    const int ci = map_index(gi, nx, sc.bc_x);
+    const long long r0 = (long long)j * nx, rs = (long long)map_index(j - 1, ny, sc.bc_y) * nx,
+                    rn = (long long)map_index(j + 1, ny, sc.bc_y) * nx;
+#pragma unroll
+    for (int q = 0; q < 20; ++q) own[q] = at(q, r0, ci);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      south[q] = at(q, rs, ci);
+      south[4 + q] = at(12 + q, rs, ci);
+      north[q] = at(q, rn, ci);
+      north[4 + q] = at(16 + q, rn, ci);
+    }
+    if constexpr (LMP) {
+      const long long rs2 = (long long)map_index(j - 2, ny, sc.bc_y) * nx,
+                      rn2 = (long long)map_index(j + 2, ny, sc.bc_y) * nx;
+      south2[0] = at(0, rs2, ci);
+      south2[1] = at(2, rs2, ci);
+      north2[0] = at(0, rn2, ci);
+      north2[1] = at(2, rn2, ci);
+    }
+    if (first || last) {
+      const int hc = map_index(first ? x0 - 1 : x0 + 64, nx, sc.bc_x), hs = first ? 4 : 8;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        halo[q] = at(q, r0, hc);
+        halo[4 + q] = at(hs + q, r0, hc);
+      }
+      if constexpr (LMP) {
+        const int oc = map_index(first ? x0 - 2 : x0 + 65, nx, sc.bc_x);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          hsouth[q] = at(q, rs, hc);
+          hnorth[q] = at(q, rn, hc);
+        }
+        outer[0] = at(0, r0, oc);
+        outer[1] = at(1, r0, oc);
+      }
+    }
+  }
+  // the slot that this step raises: a value read early only spares work (the
+  // slot grows within a step)
+  const unsigned long long seen =
+      __hip_atomic_load(&shard->lam[(A.slot + 1) % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (!BND) K = step_const<T, C>(sc, lam);
+  K = uniform_const(K);
+
+  if (xs == 0 && j == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
+
+  C u[4], uk[4][4], hu[4], hk[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    u[c] = (C)own[c];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) uk[k][c] = (C)own[4 + 4 * k + c];
+    hu[c] = (C)halo[c];
+    hk[c] = (C)halo[4 + c];
+  }
+  C f[4], g[4], hf[4], hg[4];
+  fluxes(u, K.gm1, f, g);
+  fluxes(hu, K.gm1, hf, hg);
+  // M_k + d_k of the own cell, recomputed where they are used
+  auto M_of = [&](int k, int c) { return maxw(k, u[c], f[c], g[c], K.w, K.r2a); };
+  // density of the face state between cells of densities rl, rr and momenta
+  // ml, mr along the face's normal (eq. (12); f^rho = m_1, g^rho = m_2)
+  auto face_rho = [&](C rl, C rr, C ml, C mr) { return C(0.5) * (rl + rr) - (mr - ml) * K.r2k; };
+
+  // density bounds (eq. (29)) of the cell, of its neighbours in x (through the
+  // lanes; the halo cell's by the edge lanes) and of those in y
+  C mu = C(0), nu = C(0), hmu = C(0), hnu = C(0), smu = C(0), snu = C(0), nmu = C(0), nnu = C(0);
+  C muE = C(0), nuE = C(0);
+  if constexpr (LMP) {
+    auto bounds = [](C r, C w, C e, C s, C n, C& lo, C& hi) {
+      lo = vmin(vmin(vmin(vmin(r, w), e), s), n);
+      hi = vmax(vmax(vmax(vmax(r, w), e), s), n);
+    };
+    const C us0 = (C)south[0], us1 = (C)south[1], us2 = (C)south[2];
+    const C un0 = (C)north[0], un1 = (C)north[1], un2 = (C)north[2];
+    const C hs0 = (C)hsouth[0], hs1 = (C)hsouth[1], hs2 = (C)hsouth[2];
+    const C hn0 = (C)hnorth[0], hn1 = (C)hnorth[1], hn2 = (C)hnorth[2];
+    const C orr = (C)outer[0], om = (C)outer[1];
+    const C re = face_rho(u[0], from_right_or(u[0], hu[0]), u[1], from_right_or(u[1], hu[1]));
+    const C rw = face_rho(hu[0], u[0], hu[1], u[1]);  // lane 0: the strip's west edge face
+    const C rs = face_rho(us0, u[0], us2, u[2]), rn = face_rho(u[0], un0, u[2], un2);
+    bounds(u[0], from_left_or(re, rw), re, rs, rn, mu, nu);
+    // halo cell: lane 0 the west one (its east face is the strip's west edge
+    // face), lane 63 the east one (its west face is the lane's east face)
+    const C xout = first ? face_rho(orr, hu[0], om, hu[1]) : face_rho(hu[0], orr, hu[1], om);
+    const C xin = first ? rw : re;
+    bounds(hu[0], first ? xout : xin, first ? xin : xout, face_rho(hs0, hu[0], hs2, hu[2]),
+           face_rho(hu[0], hn0, hu[2], hn2), hmu, hnu);
+    muE = from_right_or(mu, hmu);
+    nuE = from_right_or(nu, hnu);
+    // the rows below and above
+    const C se = face_rho(us0, from_right_or(us0, hs0), us1, from_right_or(us1, hs1));
+    const C sw = from_left_or(se, face_rho(hs0, us0, hs1, us1));
+    bounds(us0, sw, se, face_rho((C)south2[0], us0, (C)south2[1], us2), rs, smu, snu);
+    const C ne = face_rho(un0, from_right_or(un0, hn0), un1, from_right_or(un1, hn1));
+    const C nw = from_left_or(ne, face_rho(hn0, un0, hn1, un1));
+    bounds(un0, nw, ne, rn, face_rho(un0, (C)north2[0], un2, (C)north2[1]), nmu, nnu);
+  }
+
+  const bool here = sponge && in_sponge(sc, gi, j, nx, ny);
+  auto store = [&](int q, C v) {
+    if (!lane_out) return;
+    if constexpr (BLK)
+      put(dbase + ((long long)j * nx + x0) * 20 + q * 64 + lane, (T)v);
+    else
+      put(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
+  };
+  unsigned n_guard = 0, n_lim = 0;
+
+  // The faces one after the other (the barriers keep the compiler from
+  // overlapping them: the registers of one face at a time are what lets
+  // several waves share a SIMD).  Each leaves the new distribution that came in
+  // through it and its term of the moment sum (eqs. (25), (27)): the incoming
+  // distribution minus theta times the own one leaving through the face.
+  C ts[4], tn[4];
+  {  // south, j - 1/2
+    C v[4], w3[4], fy[4], gy[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = (C)south[c];
+      w3[c] = (C)south[4 + c];
+    }
+    fluxes(v, K.gm1, fy, gy);
+    C st[4], dG[4], M3[4], d3[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      M3[c] = maxw(2, v[c], fy[c], gy[c], K.w, K.r2a);
+      d3[c] = M3[c] - w3[c];
+      st[c] = C(0.5) * (v[c] + u[c]) - (g[c] - gy[c]) * K.r2k;
+      dG[c] = K.ac * (d3[c] - (M_of(3, c) - uk[3][c]));
+    }
+    int gd;
+    double th = face_theta<LIMS>(sc, st, dG, K.kappa, smu, snu, mu, nu, gd);
+    if (here || (sponge && in_sponge(sc, gi, j - 1, nx, ny))) th = 0.0;
+    n_guard += wave_count(lane_out && gd);
+    n_lim += wave_count(lane_out && th < 1.0);
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (lane_out) A.theta_y[(long long)j * nx + gi] = th;
+    }
+    const C tB = (C)th;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C u3n = M3[c] + tB * d3[c];
+      ts[c] = u3n - tB * (M_of(3, c) - uk[3][c]);
+      store(12 + c, u3n);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  {  // north, j + 1/2
+    C v[4], w4[4], fy[4], gy[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = (C)north[c];
+      w4[c] = (C)north[4 + c];
+    }
+    fluxes(v, K.gm1, fy, gy);
+    C st[4], dG[4], M4[4], d4[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      M4[c] = maxw(3, v[c], fy[c], gy[c], K.w, K.r2a);
+      d4[c] = M4[c] - w4[c];
+      st[c] = C(0.5) * (u[c] + v[c]) - (gy[c] - g[c]) * K.r2k;
+      dG[c] = K.ac * ((M_of(2, c) - uk[2][c]) - d4[c]);
+    }
+    int gd;
+    double th = face_theta<LIMS>(sc, st, dG, K.kappa, mu, nu, nmu, nnu, gd);
+    if (here || (sponge && in_sponge(sc, gi, j + 1, nx, ny))) th = 0.0;
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (lane_out && j == ny - 1) A.theta_y[(long long)ny * nx + gi] = th;
+    }
+    const C tT = (C)th;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C u4n = M4[c] + tT * d4[c];
+      tn[c] = u4n - tT * (M_of(2, c) - uk[2][c]);
+      store(16 + c, u4n);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  // faces counted here: the x-face i+1/2 of lanes 0..62, the west edge face
+  // (lane 0) and the south face of every lane
+  double th_edge;
+  {  // the strip's west edge, x0 - 1/2 (lane 0)
+    C st[4], dF[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C hd1 = maxw(0, hu[c], hf[c], hg[c], K.w, K.r2a) - hk[c];
+      st[c] = C(0.5) * (hu[c] + u[c]) - (f[c] - hf[c]) * K.r2k;
+      dF[c] = K.ac * (hd1 - (M_of(1, c) - uk[1][c]));
+    }
+    int gd;
+    th_edge = face_theta<LIMS>(sc, st, dF, K.kappa, hmu, hnu, mu, nu, gd);
+    if (sponge && (in_sponge(sc, x0 - 1, j, nx, ny) || in_sponge(sc, x0, j, nx, ny))) th_edge = 0.0;
+    n_guard += wave_count(first && gd);
+    n_lim += wave_count(first && th_edge < 1.0);
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (first) A.theta_x[(long long)j * (nx + 1) + x0] = th_edge;
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  C fin[4];
+  {  // east, i + 1/2
+    C st[4], dF[4], M2E[4], d2E[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C uE = from_right_or(u[c], hu[c]);
+      const C fE = from_right_or(f[c], hf[c]);
+      M2E[c] = maxw(1, uE, fE, fE, K.w, K.r2a);
+      d2E[c] = M2E[c] - from_right_or(uk[1][c], hk[c]);
+      st[c] = C(0.5) * (u[c] + uE) - (fE - f[c]) * K.r2k;
+      dF[c] = K.ac * ((M_of(0, c) - uk[0][c]) - d2E[c]);
+    }
+    int gd;
+    double th = face_theta<LIMS>(sc, st, dF, K.kappa, mu, nu, muE, nuE, gd);
+    if (here || (sponge && in_sponge(sc, gi + 1, j, nx, ny))) th = 0.0;
+    const bool inner = !last && gi + 1 < nx;
+    n_guard += wave_count(inner && gd);
+    n_lim += wave_count(inner && th < 1.0);
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (gi + 1 <= nx) A.theta_x[(long long)j * (nx + 1) + gi + 1] = th;
+    }
+    const C tR = (C)th;
+    const C tL = from_left_or(tR, (C)th_edge);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C M1 = M_of(0, c), d1 = M1 - uk[0][c];
+      const C hM1 = maxw(0, hu[c], hf[c], hg[c], K.w, K.r2a), hd1 = hM1 - hk[c];
+      const C u1n = from_left_or(M1 + tR * d1, hM1 + tL * hd1);
+      const C u2n = M2E[c] + tR * d2E[c];
+      C sum = K.alpha * u[c];
+      sum = sum + (u1n - tL * (M_of(1, c) - uk[1][c]));
+      sum = sum + (u2n - tR * d1);
+      sum = sum + ts[c];
+      fin[c] = sum + tn[c];
+      store(4 + c, u1n);
+      store(8 + c, u2n);
+      store(c, fin[c]);
+    }
+  }
+
+  // wavespeed of the stored new state, in float64; event counts by ballots
+  const double q0 = (double)(T)fin[0], q1 = (double)(T)fin[1], q2 = (double)(T)fin[2], q3 = (double)(T)fin[3];
+  const double l = cell_wavespeed(q0, q1, q2, q3, sc.gamma);
+  const bool bad = lane_out && l < 0.0;
+  unsigned n_bad = 0, n_nf = 0, n_rho = 0, n_lmp = 0;
+  if (__ballot(bad)) {
+    const unsigned k = bad ? bad_class(q0, q1, q2, q3, sc.gamma) : 0u;
+    n_bad = wave_count(bad);
+    n_nf = wave_count(k >> 16);
+    n_rho = wave_count(k & 1u);
+  }
+  if constexpr (LMP) {
+    const double lo = (double)mu, hi = (double)nu;
+    n_lmp = wave_count(lane_out && ((q0 < lo - kLmpTol<T> * fabs(lo)) || (q0 > hi + kLmpTol<T> * fabs(hi))));
+  }
+  const double lw = lane_out ? l : -1.0;
+  const double known = __longlong_as_double((long long)seen);
+  RowEvents ev = {0.0, {n_bad, n_nf, n_rho, n_guard, n_lim, n_lmp}};
+  if (__ballot(lw > known)) ev.lmax = wave_max(lw);
+  return ev;
+}
+
 // The step kernel: T the state's storage type, C its arithmetic type, LMP the
 // bounds-limited march, WPE the waves per SIMD the registers are sized for,
 // LIMS a limiter set fixed at compile time (0: read from the scheme) and TH
@@ -1761,6 +2165,53 @@ void step_kernel(StepArgs A) {
       march_short_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
     else
       march_short<T, C, LIMS, TH, BND>(A, in, ii, item, xs, ys, lane);
+  }
+}
+
+// The row kernel: a workgroup of four waves takes four rows of a strip, one
+// row per wave (the strip table is built for strips of four rows).
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
+void row_kernel(StepArgs A) {
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int grp = blockIdx.x;
+  if ((A.groups & 7) == 0) {
+    const int per = A.groups >> 3;  // one contiguous range of strips per XCD
+    grp = (grp & 7) * per + (grp >> 3);
+  }
+  if (grp >= A.n_items) return;
+  int ii = 0;
+  Inst in;
+  if (A.n_inst == 1) {
+    in = A.inst0;
+  } else {
+    ii = A.item_inst[grp];
+    in = A.insts[ii];
+  }
+  const int local = (int)(grp - in.item0);
+  const int xs = local % in.xs, j = local / in.xs * kRowsPerGroup + wave;
+  Slots* const shard = shard_of(A, ii, local);
+  RowEvents ev = {0.0, {}};
+  if (j < in.ny) ev = step_row<T, C, LMP, LIMS, TH, BND, BLK>(A, in, ii, xs, j, lane, shard);
+  // one update of the slot and the counters per workgroup (every wave reaches
+  // the barrier): same-address atomics of many short waves would queue
+  __shared__ RowEvents evs[kRowsPerGroup];
+  if (lane == 0) evs[wave] = ev;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < kRowsPerGroup; ++w) {
+      ev.lmax = vmax(ev.lmax, evs[w].lmax);
+      for (int k = 0; k < 6; ++k) ev.n[k] += evs[w].n[k];
+    }
+    // (the waves left lmax at zero where the shard already held more when they
+    // began; launches of several rounds of workgroups look again)
+    double lmax = ev.lmax;
+    if (A.n_items <= 1024 && lmax > 0.0) {
+      atomicMax(&shard->lam[(A.slot + 1) % 3], (unsigned long long)__double_as_longlong(lmax));
+      lmax = 0.0;
+    }
+    publish(shard, (A.slot + 1) % 3, lmax, ev.n[0], ev.n[3], ev.n[4], ev.n[5], ev.n[1], ev.n[2]);
   }
 }
 
@@ -2174,6 +2625,22 @@ __global__ void fill_f64_kernel(double* p, double v, long long n) {
 #define VLBM_WPE_F32_LMP 2
 #endif
 
+// Waves per SIMD of the row kernel: as many as need no scratch memory (one
+// more, with 18-36 spilled registers: 512^2 float64 PP 27 against 20 us, LMP 32
+// against 25).
+#ifndef VLBM_WPE_ROW_F64
+#define VLBM_WPE_ROW_F64 3
+#endif
+#ifndef VLBM_WPE_ROW_F64_LMP
+#define VLBM_WPE_ROW_F64_LMP 2
+#endif
+#ifndef VLBM_WPE_ROW_F32
+#define VLBM_WPE_ROW_F32 4
+#endif
+#ifndef VLBM_WPE_ROW_F32_LMP
+#define VLBM_WPE_ROW_F32_LMP 4
+#endif
+
 int grid_for(long long n, long long cap = 8192) {
   long long g = (n + 255) / 256;
   if (g > cap) g = cap;
@@ -2243,6 +2710,30 @@ static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) 
   hipLaunchKernelGGL(k, grid, block, (unsigned)dma_lds_bytes<T>((int)block.x / 64), s, a);
 }
 
+// Launch of the row kernel (a.rows).  The variants are those of the marches:
+// the limiter set fixed at compile time for the sets with PP and pressure, the
+// rest and boundary descriptions with the set read at run time.
+template <class T, bool LMP, int WPE, bool BLK>
+static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
+  constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
+  constexpr int kRelaxed = 1 | 4 | 8;
+  const dim3 block(64 * kRowsPerGroup);
+  if constexpr (!BLK) {
+    if (a.bnd) {
+      hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, true, false>), grid, block, 0, s, a);
+      return;
+    }
+  }
+  if (lims == kFixed && a.theta_x)
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, true, false, BLK>), grid, block, 0, s, a);
+  else if (lims == kFixed)
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, false, false, BLK>), grid, block, 0, s, a);
+  else if (LMP && lims == kRelaxed && !a.theta_x)
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, LMP ? kRelaxed : 0, false, false, BLK>), grid, block, 0, s, a);
+  else
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, false, BLK>), grid, block, 0, s, a);
+}
+
 static bool dma_ok(const StepArgs& a) { return a.n_inst == 1 && a.inst0.nx % 64 == 0 && !a.bnd; }
 
 template <class T, bool LMP, int WPE>
@@ -2306,6 +2797,21 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
   const int lims = (a.sc.order == 2 && a.sc.sponge == 0 && a.sc.eps <= 1e-12) ? a.sc.limiters : 0;
   const dim3 block(64 * a.waves_per_group);
   const dim3 grid(a.groups);
+  if (a.rows) {
+    if (precision == 0 && lmp)
+      a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, true>(a, lims, grid, s)
+                : launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, false>(a, lims, grid, s);
+    else if (precision == 0)
+      a.blocked ? launch_rows<double, false, VLBM_WPE_ROW_F64, true>(a, lims, grid, s)
+                : launch_rows<double, false, VLBM_WPE_ROW_F64, false>(a, lims, grid, s);
+    else if (lmp)
+      a.blocked ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, true>(a, lims, grid, s)
+                : launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false>(a, lims, grid, s);
+    else
+      a.blocked ? launch_rows<float, false, VLBM_WPE_ROW_F32, true>(a, lims, grid, s)
+                : launch_rows<float, false, VLBM_WPE_ROW_F32, false>(a, lims, grid, s);
+    return hipGetLastError();
+  }
   if (precision == 0) {
     if (lmp)
       launch_step_as<double, true, VLBM_WPE_F64_LMP>(a, lims, grid, block, s);

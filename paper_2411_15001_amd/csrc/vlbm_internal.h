@@ -104,8 +104,36 @@ struct StepArgs {
   int blocked;            // src and dst hold the blocked layout (a context's own
                           // buffers; every width a multiple of 64, no boundary
                           // descriptions), else planar
+  int rows;               // 1: the row kernel (one row of a strip per wave; the
+                          // strips are kRowsPerGroup rows high and groups counts
+                          // them), 0: the marches
   Scheme sc;
 };
+
+// Rows of a strip that one workgroup of the row kernel takes, one per wave.
+constexpr int kRowsPerGroup = 4;
+
+// Whether a launch whose shape nobody set takes the row kernel; strip_rows is
+// the number of 64-column strip rows of all instances.  A march needs some
+// 1024 strips of several rows to fill the chip and spends two (four under
+// density bounds) further rows on each; the row kernel has a wave for every
+// row, evaluates the faces between rows twice and reads its neighbours' rows
+// through the caches.  Measured on the blast and the near-vacuum rarefaction,
+// us per step, row kernel against the best march: 64^2 float64 PP 7.3 / 19.7,
+// 512^2 20.2 / 24.8, 896^2 49.8 / 54.2, 960^2 74.4 / 67.7 (the two states no
+// longer fit the last-level cache); under LMP 512^2 25.3 / 32.0, 896^2 66.9 /
+// 66.1, 960^2 89.9 / 75.9; float32 state, LMP: 832^2 42.2 / 46.2, 896^2 50.5 /
+// 47.5.  Ensembles, whose march strips end ragged at every instance: 24 of
+// 128..512 (33920 strip rows) 158 / 164, 32 of them (44544) 195 / 198; under LMP
+// 64 of 40..200 (19502) 113 / 132, 10 of 200..600 (26904) 151 / 149.  With
+// boundary descriptions every row of a march checks for ghosts, here only
+// the rows and strips at the edges: float64 LMP 400^2 32.8 / 63.1, 3000^2 964 / 1145.
+inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, const Scheme& sc) {
+  if (bnd) return true;
+  const bool lmp = (sc.limiters & 6) != 0 && sc.order == 2;
+  if (n_inst > 1) return strip_rows <= (lmp ? 24000 : 40000);
+  return strip_rows <= (lmp && precision != 0 ? 11000 : 12600);
+}
 
 enum { BND_ZERO_GRADIENT = 0, BND_WALL = 1, BND_DIRICHLET = 2 };
 
