@@ -161,6 +161,7 @@ struct lbm_ctx {
   int strip_mode = 0;  // 0: every instance strip_rows; 1: matched to the instance's height
   bool manual = false;  // the launch shape was given by the caller or the tuner
   int rows = 0;         // steps run the row kernel (see use_rows)
+  int auto_rows = 64;   // rows per strip of the marches while nobody set a shape
   int waves = 4;
   int xcd = 1;
   int grid_per_cu = 0;  // 0: one wave per strip; k > 0: persistent grid of k groups per CU
@@ -208,6 +209,7 @@ lbm_status hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
 // strips while large ones keep tall strips and few re-read halo rows.
 int inst_strip_rows(const lbm_ctx* c, int ny) {
   if (c->rows) return vlbm::kRowsPerGroup;
+  if (!c->manual) return c->auto_rows;
   if (c->strip_mode == 0) return c->strip_rows;
   int h = kMinStripRows;
   while (h * 2 <= c->strip_rows && h * 2 <= ny / 4) h *= 2;
@@ -237,6 +239,11 @@ bool default_rows(const lbm_ctx* c) {
 void build_items(lbm_ctx* c) {
   std::vector<int> order(c->n_inst);
   c->rows = !c->manual && default_rows(c) ? 1 : 0;
+  c->auto_rows = vlbm::march_rows(c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
+    long long items = 0;
+    for (const Inst& in : c->insts) items += strips_x(in.nx) * strips_y(in.ny, h);
+    return items;
+  });
   for (int i = 0; i < c->n_inst; ++i) {
     order[i] = i;
     Inst& in = c->insts[i];
@@ -262,11 +269,12 @@ void build_items(lbm_ctx* c) {
   }
 }
 
-// Default strip height: the tallest of 64, 32, 16, 8, 4 rows that still
-// yields one full round of strips (one wave each) over the chip's 1024 SIMDs
-// at the step kernel's occupancy (1 wave per SIMD in float64, 2 with the
-// float32 state), so that small grids are cut into enough waves while large
-// ones keep the re-read halo rows per strip few.  lbm_autotune refines it.
+// The strip height that lbm_get_launch reports for a new context: the tallest
+// of 64, 32, 16, 8, 4 rows that still yields one full round of strips (one
+// wave each) over the chip's 1024 SIMDs at the step kernel's occupancy (1 wave
+// per SIMD in float64, 2 with the float32 state).  Until a caller or the tuner
+// sets a shape, steps run the row kernel (use_rows) or the marches at the
+// height of march_rows.
 int default_strip_rows(const lbm_ctx* c) {
   const long long want = c->p.precision == LBM_FP64 ? 1024 : 2048;
   int rows = 64;

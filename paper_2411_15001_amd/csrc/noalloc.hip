@@ -64,17 +64,6 @@ lbm_status fail(lbm_status s, const char* m) {
   return s;
 }
 
-// Rows per strip: the tallest of 64, 32, 16, 8, 4 that still gives one wave
-// per SIMD of the chip (1024 SIMDs; 2 waves per SIMD with the float32 state),
-// the default of a new context.
-int strip_rows(int nx, int ny, int precision) {
-  const long long want = precision == LBM_FP64 ? 1024 : 2048;
-  int rows = 64;
-  for (; rows > 4; rows /= 2)
-    if ((long long)((nx + 63) / 64) * ((ny + rows - 1) / rows) >= want) break;
-  return rows;
-}
-
 }  // namespace
 
 extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev, void* dst_dev,
@@ -101,7 +90,10 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   in.ny = p->ny;
   in.xs = (p->nx + 63) / 64;
   const int rows = vlbm::use_rows((long long)in.xs * p->ny, 1, false, p->precision, sc) ? 1 : 0;
-  in.strip_h = rows ? vlbm::kRowsPerGroup : strip_rows(p->nx, p->ny, p->precision);
+  in.strip_h = rows ? vlbm::kRowsPerGroup
+                    : vlbm::march_rows(p->precision, (p->limiters & 6u) != 0 && p->order == 2, [&](int h) {
+                        return (long long)in.xs * ((p->ny + h - 1) / h);
+                      });
   in.ys = (p->ny + in.strip_h - 1) / in.strip_h;
 
   // zero the record, lambda^n of src into slot 0, then clear the counters

@@ -135,6 +135,41 @@ inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, 
   return strip_rows <= (lmp && precision != 0 ? 11000 : 12600);
 }
 
+// Rows per strip of a march whose launch shape nobody set: the height with the
+// least estimated time.  `strips(h)` gives the number of strips of height h.
+// One round of 1024 waves (float64; 2048 with the float32 state: one or two a
+// SIMD) takes a time proportional to the strip's rows and e rows of halo, with
+// the float32 state and PP a little more per row on tall strips (1 + g h); a
+// round that fills only a part phi of the chip runs faster per row, but not
+// below a fraction c of a full one, since a lone wave's chain of rows takes
+// that long.  c, e and g are fitted to 240 timings (15 grids of 960^2 to
+// 8192^2 and 4 : 1, strips of 4 to 64 rows, the four classes): the height
+// chosen is within 1.1% of the best on average, 13% at worst.  The tallest
+// strips that fill one round, the rule before, left a nearly empty second
+// round where a little more than one was needed: 1536^2 float64 PP 215 us a
+// step with strips of 32 rows (1.13 rounds), 161 with 12 (3 rounds); 3072^2
+// float32 PP 399 with 64 and 309 with 24; 3072^2 float64 LMP 720 / 604.
+template <class Strips>
+int march_rows(int precision, bool lmp, const Strips& strips) {
+  const double slots = precision == 0 ? 1024.0 : 2048.0;
+  const double c = lmp ? 0.44 : (precision == 0 ? 0.54 : 0.58);
+  const double e = precision == 0 ? (lmp ? 1.5 : 0.75) : (lmp ? 0.75 : 0.5);
+  const double g = precision != 0 && !lmp ? 0.001 : 0.0;
+  int best = 4;
+  double least = 0.0;
+  for (int h : {4, 8, 12, 16, 24, 32, 48, 64}) {
+    const double rounds = (double)strips(h) / slots;
+    const double full = __builtin_floor(rounds), phi = rounds - full;
+    const double part = phi > 0.0 ? __builtin_cbrt(phi * phi * phi + c * c * c) : 0.0;
+    const double t = (full + part) * (h + e) * (1.0 + g * h);
+    if (h == 4 || t <= least) {
+      least = t;
+      best = h;
+    }
+  }
+  return best;
+}
+
 enum { BND_ZERO_GRADIENT = 0, BND_WALL = 1, BND_DIRICHLET = 2 };
 
 // Launchers (step.hip).

@@ -115,8 +115,18 @@ def test_both_sides_of_the_size_rule(nx, ny, rows, gpu):
     groups = B.lbm_get_grid(s.ctx)[1]
     assert (groups == (nx // 64) * ((ny + 3) // 4)) == rows
     s.close()
-    a, b = run(u0, kw, None, steps=3), run(u0, kw, (16, 4), steps=3)
+    a, b = run(u0, kw, None, steps=3), run(u0, kw, (8, 2), steps=3)
     check(a, b, gpu)
+
+
+@pytest.mark.parametrize("nx,ny", [(1100, 1030), (1024, 2048)])
+@pytest.mark.parametrize("lims,prec", [(9, 0), (11, 0), (9, 1), (13, 1)])
+def test_chosen_strip_height_keeps_the_results(nx, ny, lims, prec, gpu):
+    """Grids beyond the row kernel: the strip height that the library picks
+    while nobody sets one, ragged and full strips, against a given one."""
+    u0 = np.ascontiguousarray(cases.double_rarefaction(max(nx, ny))[:, :ny, :nx])
+    kw = dict(limiters=lims, bc_x=1, bc_y=1, precision=prec)
+    check(run(u0, kw, None, steps=3), run(u0, kw, (20, 3), steps=3), gpu)
 
 
 def test_autotuned_choice_keeps_the_results(gpu, tmp_path):
