@@ -92,11 +92,23 @@ __device__ __forceinline__ int edge_kind(const uint8_t* k, int r) {
   return k ? (int)k[r] : BND_ZERO_GRADIENT;
 }
 
-// EDGES: the context has an outflow axis (the edge terms above); periodic
-// contexts run without them.  kinds: the boundary descriptions per side
-// (west, east, south, north; NULL: zero-gradient).
+// EDGES: the context has an outflow axis (the edge terms above, evaluated by
+// the cells at an edge alone); periodic contexts run without them.  kinds: the
+// boundary descriptions per side (west, east, south, north; NULL:
+// zero-gradient).
+//
+// One cell per thread; a workgroup of four waves takes 64 columns x 4 rows and
+// consecutive workgroups stay on one XCD.  What bounds it is the traffic (U's
+// moments, the factors, 20 values of the adjoint in and out: 384 bytes a cell,
+// more than half of it from the last-level cache at 512^2): the ubar'
+// of the rows above and below, 8 of 28 values read, come from the L1 and the
+// XCD's L2 where neighbouring rows run there: 21.9 us a step at 512^2 with
+// rows of 256 columns dealt to the XCDs in turn, 20.1 so (5.0 TB/s; a copy of
+// this size through the same cache reaches 5.4).  The edge terms in a branch of
+// their own take the outflow kernel from 178 to 145 registers (2 to 3 waves a
+// SIMD).
 template <bool EDGES>
-__global__ __launch_bounds__(256) void adjoint_step_kernel(Scheme sc, int nx, int ny, long long P,
+__global__ __launch_bounds__(256) void adjoint_step_kernel(Scheme sc, int nx, int ny, int xs, long long P,
                                                            const double* __restrict__ U,
                                                            const double* __restrict__ B1,
                                                            double* __restrict__ B0,
@@ -104,8 +116,12 @@ __global__ __launch_bounds__(256) void adjoint_step_kernel(Scheme sc, int nx, in
                                                            const double* __restrict__ ty,
                                                            const Slots* sl, int slot,
                                                            BndKinds kinds) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int j = blockIdx.y;
+  // groups go round-robin over the 8 XCDs: one contiguous range to each (the
+  // grid is a multiple of 8)
+  const int per = gridDim.x >> 3;
+  const int grp = (blockIdx.x & 7) * per + (blockIdx.x >> 3);
+  const int i = (grp % xs) * 64 + threadIdx.x;
+  const int j = (grp / xs) * 4 + threadIdx.y;
   if (i >= nx || j >= ny) return;
   const double a = kinetic_speed(sc, sl, slot);
   const double w = 0.25 * (1.0 - sc.alpha);
@@ -120,57 +136,82 @@ __global__ __launch_bounds__(256) void adjoint_step_kernel(Scheme sc, int nx, in
   const long long cS = (long long)js * nx + i, cN = (long long)jn * nx + i;
   const double tW = tx[(long long)j * (nx + 1) + i], tE = tx[(long long)j * (nx + 1) + i + 1];
   const double tS = ty[(long long)j * nx + i], tN = ty[(long long)(j + 1) * nx + i];
-  // kinds of the ghosts beyond this cell's edges
-  const int kw = gw ? edge_kind(kinds.k[0], j) : -1, ke = ge ? edge_kind(kinds.k[1], j) : -1;
-  const int ks = gs ? edge_kind(kinds.k[2], i) : -1, kn = gn ? edge_kind(kinds.k[3], i) : -1;
   // g1..g4: adjoint reaching u_k' of the neighbour that reads this cell
-  // (0 for a ghost); h1..h4: this cell's own g_k, read back through a
-  // zero-gradient ghost; m1..m4: the same through a wall ghost, mirrored
-  double u[4], ub[4], g1[4], g2[4], g3[4], g4[4], h1[4], h2[4], h3[4], h4[4];
-  double m1[4], m2[4], m3[4], m4[4];
+  // (0 for a ghost)
+  double u[4], ub[4], g1[4], g2[4], g3[4], g4[4];
+#pragma unroll
   for (int c = 0; c < 4; ++c) {
     u[c] = U[c * P + cX];
     ub[c] = B1[c * P + cX];
-    g1[c] = ge ? 0.0 : B1[(4 + c) * P + cE] + B1[c * P + cE];
-    g2[c] = gw ? 0.0 : B1[(8 + c) * P + cW] + B1[c * P + cW];
-    g3[c] = gn ? 0.0 : B1[(12 + c) * P + cN] + B1[c * P + cN];
-    g4[c] = gs ? 0.0 : B1[(16 + c) * P + cS] + B1[c * P + cS];
-    const double o1 = (kw >= 0 && kw != BND_DIRICHLET) ? B1[(4 + c) * P + cX] + ub[c] : 0.0;
-    const double o2 = (ke >= 0 && ke != BND_DIRICHLET) ? B1[(8 + c) * P + cX] + ub[c] : 0.0;
-    const double o3 = (ks >= 0 && ks != BND_DIRICHLET) ? B1[(12 + c) * P + cX] + ub[c] : 0.0;
-    const double o4 = (kn >= 0 && kn != BND_DIRICHLET) ? B1[(16 + c) * P + cX] + ub[c] : 0.0;
-    h1[c] = kw == BND_ZERO_GRADIENT ? o1 : 0.0;
-    h2[c] = ke == BND_ZERO_GRADIENT ? o2 : 0.0;
-    h3[c] = ks == BND_ZERO_GRADIENT ? o3 : 0.0;
-    h4[c] = kn == BND_ZERO_GRADIENT ? o4 : 0.0;
-    // R: the x-mirror negates m_1, the y-mirror m_2
-    m1[c] = kw == BND_WALL ? (c == 1 ? -o1 : o1) : 0.0;
-    m2[c] = ke == BND_WALL ? (c == 1 ? -o2 : o2) : 0.0;
-    m3[c] = ks == BND_WALL ? (c == 2 ? -o3 : o3) : 0.0;
-    m4[c] = kn == BND_WALL ? (c == 2 ? -o4 : o4) : 0.0;
+    g1[c] = B1[(4 + c) * P + cE] + B1[c * P + cE];
+    g2[c] = B1[(8 + c) * P + cW] + B1[c * P + cW];
+    g3[c] = B1[(12 + c) * P + cN] + B1[c * P + cN];
+    g4[c] = B1[(16 + c) * P + cS] + B1[c * P + cS];
+    if (EDGES) {
+      g1[c] = ge ? 0.0 : g1[c];
+      g2[c] = gw ? 0.0 : g2[c];
+      g3[c] = gn ? 0.0 : g3[c];
+      g4[c] = gs ? 0.0 : g4[c];
+    }
+  }
+  double z1[4], z2[4], z3[4], z4[4], o1[4], o2[4], o3[4], o4[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    z1[c] = (1.0 + tE) * g1[c] - tE * ub[c];
+    z2[c] = (1.0 + tW) * g2[c] - tW * ub[c];
+    z3[c] = (1.0 + tN) * g3[c] - tN * ub[c];
+    z4[c] = (1.0 + tS) * g4[c] - tS * ub[c];
+    o1[c] = tE * (ub[c] - g1[c]);
+    o2[c] = tW * (ub[c] - g2[c]);
+    o3[c] = tN * (ub[c] - g3[c]);
+    o4[c] = tS * (ub[c] - g4[c]);
+  }
+  if (EDGES && (gw || ge || gs || gn)) {
+    // kinds of the ghosts beyond this cell's edges
+    const int kw = gw ? edge_kind(kinds.k[0], j) : -1, ke = ge ? edge_kind(kinds.k[1], j) : -1;
+    const int ks = gs ? edge_kind(kinds.k[2], i) : -1, kn = gn ? edge_kind(kinds.k[3], i) : -1;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      // this cell's own g_k, read back through a zero-gradient ghost (h), or
+      // mirrored through a wall ghost (m; R: the x-mirror negates m_1, the
+      // y-mirror m_2)
+      const double q1 = (kw >= 0 && kw != BND_DIRICHLET) ? B1[(4 + c) * P + cX] + ub[c] : 0.0;
+      const double q2 = (ke >= 0 && ke != BND_DIRICHLET) ? B1[(8 + c) * P + cX] + ub[c] : 0.0;
+      const double q3 = (ks >= 0 && ks != BND_DIRICHLET) ? B1[(12 + c) * P + cX] + ub[c] : 0.0;
+      const double q4 = (kn >= 0 && kn != BND_DIRICHLET) ? B1[(16 + c) * P + cX] + ub[c] : 0.0;
+      const double h1 = kw == BND_ZERO_GRADIENT ? q1 : 0.0, m1 = kw == BND_WALL ? (c == 1 ? -q1 : q1) : 0.0;
+      const double h2 = ke == BND_ZERO_GRADIENT ? q2 : 0.0, m2 = ke == BND_WALL ? (c == 1 ? -q2 : q2) : 0.0;
+      const double h3 = ks == BND_ZERO_GRADIENT ? q3 : 0.0, m3 = ks == BND_WALL ? (c == 2 ? -q3 : q3) : 0.0;
+      const double h4 = kn == BND_ZERO_GRADIENT ? q4 : 0.0, m4 = kn == BND_WALL ? (c == 2 ? -q4 : q4) : 0.0;
+      z1[c] = z1[c] + (1.0 + tW) * h1 + (1.0 + tE) * m2;
+      z2[c] = z2[c] + (1.0 + tE) * h2 + (1.0 + tW) * m1;
+      z3[c] = z3[c] + (1.0 + tS) * h3 + (1.0 + tN) * m4;
+      z4[c] = z4[c] + (1.0 + tN) * h4 + (1.0 + tS) * m3;
+      o1[c] = o1[c] - tW * h1 - tE * m2;
+      o2[c] = o2[c] - tE * h2 - tW * m1;
+      o3[c] = o3[c] - tS * h3 - tN * m4;
+      o4[c] = o4[c] - tN * h4 - tS * m3;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    B0[(4 + c) * P + cX] = o1[c];
+    B0[(8 + c) * P + cX] = o2[c];
+    B0[(12 + c) * P + cX] = o3[c];
+    B0[(16 + c) * P + cX] = o4[c];
   }
   const Jac J = jac_of(u, sc.gamma);
-  double z1[4], z2[4], z3[4], z4[4];
-  for (int c = 0; c < 4; ++c) {
-    z1[c] = (1.0 + tE) * g1[c] - tE * ub[c] + (1.0 + tW) * h1[c] + (1.0 + tE) * m2[c];
-    z2[c] = (1.0 + tW) * g2[c] - tW * ub[c] + (1.0 + tE) * h2[c] + (1.0 + tW) * m1[c];
-    z3[c] = (1.0 + tN) * g3[c] - tN * ub[c] + (1.0 + tS) * h3[c] + (1.0 + tN) * m4[c];
-    z4[c] = (1.0 + tS) * g4[c] - tS * ub[c] + (1.0 + tN) * h4[c] + (1.0 + tS) * m3[c];
-  }
   double dx[4], dy[4], ax[4], by[4];
+#pragma unroll
   for (int c = 0; c < 4; ++c) {
     dx[c] = z1[c] - z2[c];
     dy[c] = z3[c] - z4[c];
   }
   At(J, dx, ax);
   Bt(J, dy, by);
-  for (int c = 0; c < 4; ++c) {
+#pragma unroll
+  for (int c = 0; c < 4; ++c)
     B0[c * P + cX] = sc.alpha * ub[c] + w * (z1[c] + z2[c] + z3[c] + z4[c]) + r2a * (ax[c] + by[c]);
-    B0[(4 + c) * P + cX] = tE * (ub[c] - g1[c]) - tW * h1[c] - tE * m2[c];
-    B0[(8 + c) * P + cX] = tW * (ub[c] - g2[c]) - tE * h2[c] - tW * m1[c];
-    B0[(12 + c) * P + cX] = tN * (ub[c] - g3[c]) - tS * h3[c] - tN * m4[c];
-    B0[(16 + c) * P + cX] = tS * (ub[c] - g4[c]) - tN * h4[c] - tS * m3[c];
-  }
 }
 
 // u0bar = Ubar0[u] + sum_k J_{M_k}(u0)^T Ubar0[u_k] with a^0 fixed.
@@ -206,13 +247,15 @@ __global__ __launch_bounds__(256) void adjoint_init_kernel(Scheme sc, long long 
 hipError_t launch_adjoint_step(const Scheme& sc, const Inst& in, long long plane, const double* U,
                                const double* Ub1, double* Ub0, const double* tx, const double* ty,
                                const Slots* slots, int slot, const BndKinds& kinds, hipStream_t s) {
-  const dim3 block(256);
-  const dim3 grid((in.nx + 255) / 256, in.ny);
+  const int xs = (in.nx + 63) / 64;
+  const long long groups = (long long)xs * ((in.ny + 3) / 4);
+  const dim3 block(64, 4);
+  const dim3 grid((unsigned)((groups + 7) / 8 * 8));
   if (sc.bc_x == 1 || sc.bc_y == 1)
-    hipLaunchKernelGGL(adjoint_step_kernel<true>, grid, block, 0, s, sc, in.nx, in.ny, plane, U, Ub1,
+    hipLaunchKernelGGL(adjoint_step_kernel<true>, grid, block, 0, s, sc, in.nx, in.ny, xs, plane, U, Ub1,
                        Ub0, tx, ty, slots, slot, kinds);
   else
-    hipLaunchKernelGGL(adjoint_step_kernel<false>, grid, block, 0, s, sc, in.nx, in.ny, plane, U, Ub1,
+    hipLaunchKernelGGL(adjoint_step_kernel<false>, grid, block, 0, s, sc, in.nx, in.ny, xs, plane, U, Ub1,
                        Ub0, tx, ty, slots, slot, kinds);
   return hipGetLastError();
 }
