@@ -289,6 +289,14 @@ __device__ __forceinline__ double wave_max(double v) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// The same value, which the compiler takes for a new one: what follows from it
+// is computed again instead of kept.
+template <class X>
+__device__ __forceinline__ X anew(X v) {
+  __asm__ volatile("" : "+v"(v));
+  return v;
+}
+
 __device__ __forceinline__ unsigned wave_count(bool b) { return (unsigned)__popcll(__ballot(b)); }
 
 // The records that the waves of instance ii raise (see Slots): record `k & mask`.
@@ -1748,6 +1756,101 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
 
 // ------------------------------------------------------------- one row per wave
 
+struct RowEvents {
+  double lmax;
+  unsigned n[6];  // bad, non-finite, rho <= 0, guard, limited, lmp
+};
+
+// What a row beside the grid's edge reads, ghosts included (see step_row for the
+// arrays).
+template <class T, class C, bool LMP>
+__device__ __forceinline__ void row_ghosts(const StepArgs& A, const BndDesc& bd, const Inst& in, const T* __restrict__ sbase,
+                                           long long P, int x0, int j, int lane, const StepConst<T, C>& K, T (&own)[20],
+                                           T (&south)[8], T (&north)[8], T (&south2)[2], T (&north2)[2], T (&halo)[8],
+                                           T (&hsouth)[3], T (&hnorth)[3], T (&outer)[2]) {
+  const int nx = in.nx, gi = x0 + lane;
+  const bool first = lane == 0, last = lane == 63;
+#pragma unroll 1
+  for (int dr = LMP ? -2 : -1; dr <= (LMP ? 2 : 1); ++dr) {
+    T t[20];
+    bnd_cell<T, C>(A, bd, in, sbase, P, min(gi, nx + 1), j + dr, K, t);
+    if (dr == 0) {
+#pragma unroll
+      for (int q = 0; q < 20; ++q) own[q] = t[q];
+    } else if (dr == -1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        south[q] = t[q];
+        south[4 + q] = t[12 + q];
+      }
+    } else if (dr == 1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        north[q] = t[q];
+        north[4 + q] = t[16 + q];
+      }
+    } else if (dr == -2) {
+      south2[0] = t[0];
+      south2[1] = t[2];
+    } else {
+      north2[0] = t[0];
+      north2[1] = t[2];
+    }
+  }
+  if (first || last) {
+#pragma unroll 1
+    for (int k = LMP ? 0 : 1; k < (LMP ? 4 : 2); ++k) {
+      // the halo cell of rows j - 1, j, j + 1 and the outer cell of row j
+      const int c = first ? (k == 3 ? x0 - 2 : x0 - 1) : min(k == 3 ? x0 + 65 : x0 + 64, nx + 1);
+      T t[20];
+      bnd_cell<T, C>(A, bd, in, sbase, P, c, k == 3 ? j : j + k - 1, K, t);
+      if (k == 1) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          halo[q] = t[q];
+          halo[4 + q] = first ? t[4 + q] : t[8 + q];
+        }
+      } else if (k == 0) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) hsouth[q] = t[q];
+      } else if (k == 2) {
+#pragma unroll
+        for (int q = 0; q < 3; ++q) hnorth[q] = t[q];
+      } else {
+        outer[0] = t[0];
+        outer[1] = t[1];
+      }
+    }
+  }
+}
+
+// The wavespeed and event counts of a finished row (new moments fin, as stored;
+// mu, nu its density bounds); seen: the lambda the shard already held.
+template <class T, bool LMP, class C>
+__device__ __forceinline__ RowEvents row_events(const Scheme& sc, const C (&fin)[4], bool lane_out, C mu, C nu,
+                                                unsigned n_guard, unsigned n_lim, unsigned long long seen) {
+  // wavespeed of the stored new state, in float64; event counts by ballots
+  const double q0 = (double)(T)fin[0], q1 = (double)(T)fin[1], q2 = (double)(T)fin[2], q3 = (double)(T)fin[3];
+  const double l = cell_wavespeed(q0, q1, q2, q3, sc.gamma);
+  const bool bad = lane_out && l < 0.0;
+  unsigned n_bad = 0, n_nf = 0, n_rho = 0, n_lmp = 0;
+  if (__ballot(bad)) {
+    const unsigned k = bad ? bad_class(q0, q1, q2, q3, sc.gamma) : 0u;
+    n_bad = wave_count(bad);
+    n_nf = wave_count(k >> 16);
+    n_rho = wave_count(k & 1u);
+  }
+  if constexpr (LMP) {
+    const double lo = (double)mu, hi = (double)nu;
+    n_lmp = wave_count(lane_out && ((q0 < lo - kLmpTol<T> * fabs(lo)) || (q0 > hi + kLmpTol<T> * fabs(hi))));
+  }
+  const double lw = lane_out ? l : -1.0;
+  const double known = __longlong_as_double((long long)seen);
+  RowEvents ev = {0.0, {n_bad, n_nf, n_rho, n_guard, n_lim, n_lmp}};
+  if (__ballot(lw > known)) ev.lmax = wave_max(lw);
+  return ev;
+}
+
 // One row of one strip: the 64 cells x0 .. x0 + 63 of row j, with everything
 // they read loaded at once: the row itself, u and u_3 of the row below, u and
 // u_4 of the row above, and with density bounds rho and m_2 of the rows two
@@ -1763,11 +1866,6 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
 // bounds it: at 64^2 a wave lives 7 us, of which 3 wait for the first loads and
 // the kernel's code and 2 issue its 1035 vector instructions; at 512^2
 // (float64, PP, 4 rows per SIMD, 3 resident) 20 us a step, 7.3 of them vector issue.
-struct RowEvents {
-  double lmax;
-  unsigned n[6];  // bad, non-finite, rho <= 0, guard, limited, lmp
-};
-
 template <class T, class C, bool LMP, int LIMS, bool TH, bool BND, bool BLK>
 __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in, int ii, int xs, int j, int lane,
                                               const Slots* shard) {
@@ -1802,61 +1900,9 @@ __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in,
   if constexpr (BND) {
     // interior rows and strips read no ghost
     plain = j >= 2 && j + 2 < ny && x0 >= 2 && x0 + 66 <= nx;
-    if (!plain) {
-      const BndDesc bd = bnd_desc(A, A.slots + ii);
-#pragma unroll 1
-      for (int dr = LMP ? -2 : -1; dr <= (LMP ? 2 : 1); ++dr) {
-        T t[20];
-        bnd_cell<T, C>(A, bd, in, sbase, P, min(gi, nx + 1), j + dr, K, t);
-        if (dr == 0) {
-#pragma unroll
-          for (int q = 0; q < 20; ++q) own[q] = t[q];
-        } else if (dr == -1) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            south[q] = t[q];
-            south[4 + q] = t[12 + q];
-          }
-        } else if (dr == 1) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            north[q] = t[q];
-            north[4 + q] = t[16 + q];
-          }
-        } else if (dr == -2) {
-          south2[0] = t[0];
-          south2[1] = t[2];
-        } else {
-          north2[0] = t[0];
-          north2[1] = t[2];
-        }
-      }
-      if (first || last) {
-#pragma unroll 1
-        for (int k = LMP ? 0 : 1; k < (LMP ? 4 : 2); ++k) {
-          // the halo cell of rows j - 1, j, j + 1 and the outer cell of row j
-          const int c = first ? (k == 3 ? x0 - 2 : x0 - 1) : min(k == 3 ? x0 + 65 : x0 + 64, nx + 1);
-          T t[20];
-          bnd_cell<T, C>(A, bd, in, sbase, P, c, k == 3 ? j : j + k - 1, K, t);
-          if (k == 1) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-              halo[q] = t[q];
-              halo[4 + q] = first ? t[4 + q] : t[8 + q];
-            }
-          } else if (k == 0) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) hsouth[q] = t[q];
-          } else if (k == 2) {
-#pragma unroll
-            for (int q = 0; q < 3; ++q) hnorth[q] = t[q];
-          } else {
-            outer[0] = t[0];
-            outer[1] = t[1];
-          }
-        }
-      }
-    }
+    if (!plain)
+      row_ghosts<T, C, LMP>(A, bnd_desc(A, A.slots + ii), in, sbase, P, x0, j, lane, K, own, south, north, south2,
+                            north2, halo, hsouth, hnorth, outer);
   }
   if (plain) {
     const int ci = map_index(gi, nx, sc.bc_x);
@@ -2101,26 +2147,317 @@ __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in,
     }
   }
 
-  // wavespeed of the stored new state, in float64; event counts by ballots
-  const double q0 = (double)(T)fin[0], q1 = (double)(T)fin[1], q2 = (double)(T)fin[2], q3 = (double)(T)fin[3];
-  const double l = cell_wavespeed(q0, q1, q2, q3, sc.gamma);
-  const bool bad = lane_out && l < 0.0;
-  unsigned n_bad = 0, n_nf = 0, n_rho = 0, n_lmp = 0;
-  if (__ballot(bad)) {
-    const unsigned k = bad ? bad_class(q0, q1, q2, q3, sc.gamma) : 0u;
-    n_bad = wave_count(bad);
-    n_nf = wave_count(k >> 16);
-    n_rho = wave_count(k & 1u);
+  return row_events<T, LMP>(sc, fin, lane_out, mu, nu, n_guard, n_lim, seen);
+}
+
+// step_row in float64 under density bounds with its registers kept to three
+// waves per SIMD (168): the x-faces first, and each y-face's values loaded only
+// when its turn comes.  step_row's 192 leave two: 384^2 18.7 us a step against
+// 15.9 here, 768^2 50.0 / 45.3, 896^2 66.7 / 62.3; where no SIMD has more than
+// one wave, up to 256 workgroups, its loads at once are better (64^2 8.0 / 8.4).
+template <int LIMS, bool TH, bool BLK>
+__device__ __forceinline__ RowEvents step_row_late(const StepArgs& A, const Inst& in, int ii, int xs, int j, int lane,
+                                                   const Slots* shard) {
+  using T = double;
+  using C = double;
+  const Scheme& sc = A.sc;
+  const int nx = in.nx, ny = in.ny;
+  const int x0 = xs * 64;
+  const int gi = x0 + lane;
+  const bool lane_out = gi < nx;
+  const bool first = lane == 0, last = lane == 63;
+  const bool sponge = LIMS == 0 && sc.sponge > 0;
+  const double lam = step_lambda(A, ii, lane);
+
+  const T* __restrict__ sbase = (const T*)A.src + in.off * (BLK ? 20 : 1);
+  T* __restrict__ dbase = (T*)A.dst + in.off * (BLK ? 20 : 1);
+  const long long P = A.plane;
+  // value q of the cell in column c of the row that starts at element r
+  // (row * nx; blocked: of the row's first 64-cell run, and a run holds 1280)
+  auto at = [&](int q, long long r, int c) -> T {
+    if constexpr (BLK)
+      return (sbase + r * 20 + q * 64)[(unsigned)(c >> 6) * 1280u + (unsigned)(c & 63)];
+    else
+      return (sbase + q * P)[(unsigned)r + (unsigned)c];
+  };
+
+  // rows j - 2 .. j + 2 of the lane's column, and of the halo column x0 - 1
+  // (lane 0) or x0 + 64 (lane 63); the outer column x0 - 2 or x0 + 65
+  T own[20], south[8], north[8], south2[2], north2[2];
+  T halo[8] = {}, hsouth[3] = {}, hnorth[3] = {}, outer[2] = {};
+  const int ci = map_index(gi, nx, sc.bc_x), hc = map_index(first ? x0 - 1 : x0 + 64, nx, sc.bc_x);
+  const long long r0 = (long long)j * nx, rs = (long long)map_index(j - 1, ny, sc.bc_y) * nx,
+                  rn = (long long)map_index(j + 1, ny, sc.bc_y) * nx;
+#pragma unroll
+  for (int q = 0; q < 12; ++q) own[q] = at(q, r0, ci);
+  if (first || last) {
+    const int hs = first ? 4 : 8;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      halo[q] = at(q, r0, hc);
+      halo[4 + q] = at(hs + q, r0, hc);
+    }
   }
-  if constexpr (LMP) {
-    const double lo = (double)mu, hi = (double)nu;
-    n_lmp = wave_count(lane_out && ((q0 < lo - kLmpTol<T> * fabs(lo)) || (q0 > hi + kLmpTol<T> * fabs(hi))));
+  south[0] = at(0, rs, ci);
+  south[2] = at(2, rs, ci);
+  north[0] = at(0, rn, ci);
+  north[2] = at(2, rn, ci);
+  if (first || last) {
+    const int oc = map_index(first ? x0 - 2 : x0 + 65, nx, sc.bc_x);
+    hsouth[0] = at(0, rs, hc);
+    hsouth[2] = at(2, rs, hc);
+    hnorth[0] = at(0, rn, hc);
+    hnorth[2] = at(2, rn, hc);
+    outer[0] = at(0, r0, oc);
+    outer[1] = at(1, r0, oc);
   }
-  const double lw = lane_out ? l : -1.0;
-  const double known = __longlong_as_double((long long)seen);
-  RowEvents ev = {0.0, {n_bad, n_nf, n_rho, n_guard, n_lim, n_lmp}};
-  if (__ballot(lw > known)) ev.lmax = wave_max(lw);
-  return ev;
+  // each y-face's values are brought in when its turn comes
+  auto load_south = [&]() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      south[q] = at(q, rs, ci);
+      south[4 + q] = at(12 + q, rs, ci);
+      own[16 + q] = at(16 + q, r0, ci);
+    }
+    const long long rs2 = (long long)map_index(j - 2, ny, sc.bc_y) * nx;
+    south2[0] = at(0, rs2, ci);
+    south2[1] = at(2, rs2, ci);
+    if (first || last) {
+      hsouth[0] = at(0, rs, hc);
+      hsouth[1] = at(1, rs, hc);
+    }
+  };
+  auto load_north = [&]() {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      north[q] = at(q, rn, ci);
+      north[4 + q] = at(16 + q, rn, ci);
+      own[12 + q] = at(12 + q, r0, ci);
+    }
+    const long long rn2 = (long long)map_index(j + 2, ny, sc.bc_y) * nx;
+    north2[0] = at(0, rn2, ci);
+    north2[1] = at(2, rn2, ci);
+    if (first || last) {
+      hnorth[0] = at(0, rn, hc);
+      hnorth[1] = at(1, rn, hc);
+    }
+  };
+  // the slot that this step raises: a value read early only spares work (the
+  // slot grows within a step)
+  const unsigned long long seen =
+      __hip_atomic_load(&shard->lam[(A.slot + 1) % 3], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const StepConst<T, C> K = uniform_const(step_const<T, C>(sc, lam));
+
+  if (xs == 0 && j == 0) begin_step(A, ii, in.dx, K.a, lam, lane);
+
+  C u[4];
+#pragma unroll
+  for (int c = 0; c < 4; ++c) u[c] = (C)own[c];
+  C f[4], g[4], unused[4];
+  fluxes(u, K.gm1, f, unused);
+  // Maxwellians of the own cell, recomputed where they are used
+  auto M_of = [&](int k, int c) { return k < 2 ? maxw(k, u[c], f[c], f[c], K.w, K.r2a) : maxw(k, u[c], g[c], g[c], K.w, K.r2a); };
+  // density of the face state between cells of densities rl, rr and momenta
+  // ml, mr along the face's normal (eq. (12); f^rho = m_1, g^rho = m_2)
+  auto face_rho = [&](C rl, C rr, C ml, C mr) { return C(0.5) * (rl + rr) - (mr - ml) * K.r2k; };
+  // density bounds (eq. (29)) of a cell from its density and its faces'
+  auto bounds = [](C r, C w, C e, C s, C n, C& lo, C& hi) {
+    lo = vmin(vmin(vmin(vmin(r, w), e), s), n);
+    hi = vmax(vmax(vmax(vmax(r, w), e), s), n);
+  };
+  const bool here = sponge && in_sponge(sc, gi, j, nx, ny);
+  auto store = [&](int q, C v) {
+    if (!lane_out) return;
+    if constexpr (BLK)
+      put(&(dbase + ((long long)j * nx + x0) * 20 + q * 64)[(unsigned)lane], (T)v);
+    else
+      put(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
+  };
+  unsigned n_guard = 0, n_lim = 0;
+  C mu = C(0), nu = C(0), rs0 = C(0), rn0 = C(0);  // bounds of the cell, density of its y-faces
+
+  // The faces one after the other (the barriers keep the compiler from
+  // overlapping them: the registers of one face at a time are what lets
+  // several waves share a SIMD).  Each adds its term to the moment sum (eqs.
+  // (25), (27)): the new distribution that came in through it minus theta
+  // times the own one leaving through it.  Faces counted here: the x-face
+  // i+1/2 of lanes 0..62, the west edge face (lane 0) and the south face of
+  // every lane.
+  C fin[4];
+  {
+    C u1[4], u2[4], hu[4], hk[4], hf[4], hg[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      u1[c] = (C)own[4 + c];
+      u2[c] = (C)own[8 + c];
+      hu[c] = (C)halo[c];
+      hk[c] = (C)halo[4 + c];
+    }
+    fluxes(hu, K.gm1, hf, hg);
+    C hmu = C(0), hnu = C(0), muE = C(0), nuE = C(0);
+    const C orr = (C)outer[0], om = (C)outer[1];
+    const C re = face_rho(u[0], from_right_or(u[0], hu[0]), u[1], from_right_or(u[1], hu[1]));
+    const C rw = face_rho(hu[0], u[0], hu[1], u[1]);  // lane 0: the strip's west edge face
+    rs0 = face_rho((C)south[0], u[0], (C)south[2], u[2]);
+    rn0 = face_rho(u[0], (C)north[0], u[2], (C)north[2]);
+    bounds(u[0], from_left_or(re, rw), re, rs0, rn0, mu, nu);
+    // halo cell: lane 0 the west one (its east face is the strip's west edge
+    // face), lane 63 the east one (its west face is the lane's east face)
+    const C xout = first ? face_rho(orr, hu[0], om, hu[1]) : face_rho(hu[0], orr, hu[1], om);
+    const C xin = first ? rw : re;
+    bounds(hu[0], first ? xout : xin, first ? xin : xout,
+           face_rho((C)hsouth[0], hu[0], (C)hsouth[2], hu[2]),
+           face_rho(hu[0], (C)hnorth[0], hu[2], (C)hnorth[2]), hmu, hnu);
+    muE = from_right_or(mu, hmu);
+    nuE = from_right_or(nu, hnu);
+    C e1[4], th_edge;  // lane 0: the new u_1 that came in through the west edge
+    {  // the strip's west edge, x0 - 1/2 (lane 0)
+      C st[4], dF[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const C hd1 = maxw(0, hu[c], hf[c], hg[c], K.w, K.r2a) - hk[c];
+        st[c] = C(0.5) * (hu[c] + u[c]) - (f[c] - hf[c]) * K.r2k;
+        dF[c] = K.ac * (hd1 - (M_of(1, c) - u2[c]));
+      }
+      int gd;
+      double th = face_theta<LIMS>(sc, st, dF, K.kappa, hmu, hnu, mu, nu, gd);
+      if (sponge && (in_sponge(sc, x0 - 1, j, nx, ny) || in_sponge(sc, x0, j, nx, ny))) th = 0.0;
+      n_guard += wave_count(first && gd);
+      n_lim += wave_count(first && th < 1.0);
+      if (TH || (LIMS == 0 && A.theta_x)) {
+        if (first) A.theta_x[(long long)j * (nx + 1) + x0] = th;
+      }
+      th_edge = uniform((C)th);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const C hM1 = maxw(0, hu[c], hf[c], hg[c], K.w, K.r2a);
+        e1[c] = uniform(hM1 + th_edge * (hM1 - hk[c]));  // lane 0's, in scalar registers
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    {  // east, i + 1/2
+      C st[4], dF[4], M2E[4], d2E[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const C uE = from_right_or(u[c], hu[c]);
+        const C fE = from_right_or(f[c], hf[c]);
+        M2E[c] = maxw(1, uE, fE, fE, K.w, K.r2a);
+        d2E[c] = M2E[c] - from_right_or(u2[c], hk[c]);
+        st[c] = C(0.5) * (u[c] + uE) - (fE - f[c]) * K.r2k;
+        dF[c] = K.ac * ((M_of(0, c) - u1[c]) - d2E[c]);
+      }
+      int gd;
+      double th = face_theta<LIMS>(sc, st, dF, K.kappa, mu, nu, muE, nuE, gd);
+      if (here || (sponge && in_sponge(sc, gi + 1, j, nx, ny))) th = 0.0;
+      const bool inner = !last && gi + 1 < nx;
+      n_guard += wave_count(inner && gd);
+      n_lim += wave_count(inner && th < 1.0);
+      if (TH || (LIMS == 0 && A.theta_x)) {
+        if (gi + 1 <= nx) A.theta_x[(long long)j * (nx + 1) + gi + 1] = th;
+      }
+      const C tR = (C)th;
+      const C tL = from_left_or(tR, th_edge);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const C M1 = M_of(0, c), d1 = M1 - u1[c];
+        const C u1n = from_left_or(M1 + tR * d1, e1[c]);
+        const C u2n = M2E[c] + tR * d2E[c];
+        C sum = K.alpha * u[c];
+        sum = sum + (u1n - tL * (M_of(1, c) - u2[c]));
+        fin[c] = sum + (u2n - tR * d1);
+        store(4 + c, u1n);
+        store(8 + c, u2n);
+      }
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  load_south();
+  // (the y-flux from the start: one more division, six registers fewer while
+  // the x-faces are evaluated)
+#pragma unroll
+  for (int c = 0; c < 4; ++c) u[c] = anew(u[c]);
+  fluxes(u, K.gm1, unused, g);
+  __builtin_amdgcn_sched_barrier(0);
+  {  // south, j - 1/2
+    C v[4], w3[4], u4[4], fy[4], gy[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = (C)south[c];
+      w3[c] = (C)south[4 + c];
+      u4[c] = (C)own[16 + c];
+    }
+    fluxes(v, K.gm1, fy, gy);
+    C lo = C(0), hi = C(0);
+    const C h0 = (C)hsouth[0], h1 = (C)hsouth[1];
+    const C se = face_rho(v[0], from_right_or(v[0], h0), v[1], from_right_or(v[1], h1));
+    const C sw = from_left_or(se, face_rho(h0, v[0], h1, v[1]));
+    bounds(v[0], sw, se, face_rho((C)south2[0], v[0], (C)south2[1], v[2]), rs0, lo, hi);
+    C st[4], dG[4], M3[4], d3[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      M3[c] = maxw(2, v[c], fy[c], gy[c], K.w, K.r2a);
+      d3[c] = M3[c] - w3[c];
+      st[c] = C(0.5) * (v[c] + u[c]) - (g[c] - gy[c]) * K.r2k;
+      dG[c] = K.ac * (d3[c] - (M_of(3, c) - u4[c]));
+    }
+    int gd;
+    double th = face_theta<LIMS>(sc, st, dG, K.kappa, lo, hi, mu, nu, gd);
+    if (here || (sponge && in_sponge(sc, gi, j - 1, nx, ny))) th = 0.0;
+    n_guard += wave_count(lane_out && gd);
+    n_lim += wave_count(lane_out && th < 1.0);
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (lane_out) A.theta_y[(long long)j * nx + gi] = th;
+    }
+    const C tB = (C)th;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C u3n = M3[c] + tB * d3[c];
+      fin[c] = fin[c] + (u3n - tB * (M_of(3, c) - u4[c]));
+      store(12 + c, u3n);
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  load_north();
+  __builtin_amdgcn_sched_barrier(0);
+  {  // north, j + 1/2
+    C v[4], w4[4], u3[4], fy[4], gy[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      v[c] = (C)north[c];
+      w4[c] = (C)north[4 + c];
+      u3[c] = (C)own[12 + c];
+    }
+    fluxes(v, K.gm1, fy, gy);
+    C lo = C(0), hi = C(0);
+    const C h0 = (C)hnorth[0], h1 = (C)hnorth[1];
+    const C ne = face_rho(v[0], from_right_or(v[0], h0), v[1], from_right_or(v[1], h1));
+    const C nw = from_left_or(ne, face_rho(h0, v[0], h1, v[1]));
+    bounds(v[0], nw, ne, rn0, face_rho(v[0], (C)north2[0], v[2], (C)north2[1]), lo, hi);
+    C st[4], dG[4], M4[4], d4[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      M4[c] = maxw(3, v[c], fy[c], gy[c], K.w, K.r2a);
+      d4[c] = M4[c] - w4[c];
+      st[c] = C(0.5) * (u[c] + v[c]) - (gy[c] - g[c]) * K.r2k;
+      dG[c] = K.ac * ((M_of(2, c) - u3[c]) - d4[c]);
+    }
+    int gd;
+    double th = face_theta<LIMS>(sc, st, dG, K.kappa, mu, nu, lo, hi, gd);
+    if (here || (sponge && in_sponge(sc, gi, j + 1, nx, ny))) th = 0.0;
+    if (TH || (LIMS == 0 && A.theta_x)) {
+      if (lane_out && j == ny - 1) A.theta_y[(long long)ny * nx + gi] = th;
+    }
+    const C tT = (C)th;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const C u4n = M4[c] + tT * d4[c];
+      fin[c] = fin[c] + (u4n - tT * (M_of(2, c) - u3[c]));
+      store(16 + c, u4n);
+      store(c, fin[c]);
+    }
+  }
+
+  return row_events<T, true>(sc, fin, lane_out, mu, nu, n_guard, n_lim, seen);
 }
 
 // The step kernel: T the state's storage type, C its arithmetic type, LMP the
@@ -2170,7 +2507,7 @@ void step_kernel(StepArgs A) {
 
 // The row kernel: a workgroup of four waves takes four rows of a strip, one
 // row per wave (the strip table is built for strips of four rows).
-template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK>
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK, bool LATE = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
 void row_kernel(StepArgs A) {
   const int lane = threadIdx.x & 63;
@@ -2193,7 +2530,12 @@ void row_kernel(StepArgs A) {
   const int xs = local % in.xs, j = local / in.xs * kRowsPerGroup + wave;
   Slots* const shard = shard_of(A, ii, local);
   RowEvents ev = {0.0, {}};
-  if (j < in.ny) ev = step_row<T, C, LMP, LIMS, TH, BND, BLK>(A, in, ii, xs, j, lane, shard);
+  if (j < in.ny) {
+    if constexpr (LATE)
+      ev = step_row_late<LIMS, TH, BLK>(A, in, ii, xs, j, lane, shard);
+    else
+      ev = step_row<T, C, LMP, LIMS, TH, BND, BLK>(A, in, ii, xs, j, lane, shard);
+  }
   // one update of the slot and the counters per workgroup (every wave reaches
   // the barrier): same-address atomics of many short waves would queue
   __shared__ RowEvents evs[kRowsPerGroup];
@@ -2634,6 +2976,9 @@ __global__ void fill_f64_kernel(double* p, double v, long long n) {
 #ifndef VLBM_WPE_ROW_F64_LMP
 #define VLBM_WPE_ROW_F64_LMP 2
 #endif
+#ifndef VLBM_WPE_ROW_F64_LATE
+#define VLBM_WPE_ROW_F64_LATE 3
+#endif
 #ifndef VLBM_WPE_ROW_F32
 #define VLBM_WPE_ROW_F32 4
 #endif
@@ -2713,25 +3058,25 @@ static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) 
 // Launch of the row kernel (a.rows).  The variants are those of the marches:
 // the limiter set fixed at compile time for the sets with PP and pressure, the
 // rest and boundary descriptions with the set read at run time.
-template <class T, bool LMP, int WPE, bool BLK>
+template <class T, bool LMP, int WPE, bool BLK, bool LATE = false>
 static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
   constexpr int kRelaxed = 1 | 4 | 8;
   const dim3 block(64 * kRowsPerGroup);
-  if constexpr (!BLK) {
+  if constexpr (!BLK && !LATE) {
     if (a.bnd) {
       hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, true, false>), grid, block, 0, s, a);
       return;
     }
   }
   if (lims == kFixed && a.theta_x)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, true, false, BLK>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, true, false, BLK, LATE>), grid, block, 0, s, a);
   else if (lims == kFixed)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, false, false, BLK>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, false, false, BLK, LATE>), grid, block, 0, s, a);
   else if (LMP && lims == kRelaxed && !a.theta_x)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, LMP ? kRelaxed : 0, false, false, BLK>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, LMP ? kRelaxed : 0, false, false, BLK, LATE>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, false, BLK>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, false, BLK, LATE>), grid, block, 0, s, a);
 }
 
 static bool dma_ok(const StepArgs& a) { return a.n_inst == 1 && a.inst0.nx % 64 == 0 && !a.bnd; }
@@ -2798,7 +3143,10 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
   const dim3 block(64 * a.waves_per_group);
   const dim3 grid(a.groups);
   if (a.rows) {
-    if (precision == 0 && lmp)
+    if (precision == 0 && lmp && a.n_items > 256 && !a.bnd)
+      a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, true, true>(a, lims, grid, s)
+                : launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, false, true>(a, lims, grid, s);
+    else if (precision == 0 && lmp)
       a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, true>(a, lims, grid, s)
                 : launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, false>(a, lims, grid, s);
     else if (precision == 0)

@@ -63,6 +63,17 @@ def test_rows_equal_marches(nx, ny, lims, prec, gpu):
         check(run(u0, kw, None), run(u0, kw, (8, 2)), gpu)
 
 
+@pytest.mark.parametrize("nx,ny", [(1, 1030), (64, 1030), (200, 1029), (1030, 66)])
+@pytest.mark.parametrize("lims", [2, 11, 13, 15])
+def test_rows_under_bounds_beyond_one_group_per_cu(nx, ny, lims, gpu):
+    """float64 under density bounds with more than 256 workgroups: the form of
+    the row kernel that loads each face's values in turn."""
+    for k, (bx, by, sponge) in enumerate([(0, 0, 0), (1, 1, 0), (1, 0, 2), (0, 1, 3)]):
+        kw = dict(limiters=lims, a_beta=1.1, bc_x=bx, bc_y=by, sponge=sponge)
+        u0 = field(nx, ny, 30 + k)
+        check(run(u0, kw, None, steps=4), run(u0, kw, (8, 2), steps=4), gpu)
+
+
 @pytest.mark.parametrize("nx,ny", [(2, 2), (65, 5), (130, 40), (64, 64)])
 @pytest.mark.parametrize("lims", [9, 13])
 @pytest.mark.parametrize("prec", [0, 1])
