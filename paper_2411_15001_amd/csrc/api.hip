@@ -824,7 +824,7 @@ lbm_status lbm_get_state(lbm_ctx* c, void* dst) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (!dst) return fail(c, LBM_EINVAL, "destination must be a device pointer");
   if (lbm_status st = require_attached(c)) return st;
-  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->n_inst, c->plane, c->cur(), dst,
+  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(), dst,
                                                     c->p.precision, 0, c->stream)
                             : hipMemcpyAsync(dst, c->cur(), lbm_state_bytes(c), hipMemcpyDeviceToDevice,
                                              c->stream);
@@ -836,7 +836,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (!src) return fail(c, LBM_EINVAL, "source must be a device pointer");
   if (src == c->cur() || src == c->other()) return fail(c, LBM_EINVAL, "src must be a caller buffer");
-  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->n_inst, c->plane, src, c->cur(),
+  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, src, c->cur(),
                                                     c->p.precision, 1, c->stream)
                             : hipMemcpyAsync(c->cur(), src, lbm_state_bytes(c), hipMemcpyDeviceToDevice,
                                              c->stream);
@@ -844,8 +844,8 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
   const int slot = (int)(c->step % 3);
   if (e == hipSuccess) e = fold_shards(c, slot);
   if (e == hipSuccess)
-    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->n_inst, c->plane, c->cur(),
-                                  c->slots, slot, c->p.precision, c->blocked, c->stream);
+    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(),
+                                  c->slots, slot, c->p.precision, c->blocked, 1, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "set_state wavespeed");
   c->detached = false;
   return LBM_OK;
@@ -956,7 +956,7 @@ lbm_status lbm_set_instance_boundary(lbm_ctx* c, int32_t inst, int32_t side, con
     // the kernels that read descriptions take the planar layout: convert the
     // current state once, through the other buffer (which the next step
     // overwrites anyway), and stay planar
-    hipError_t e = vlbm::launch_relayout(c->insts.data(), c->n_inst, c->plane, c->cur(), c->other(),
+    hipError_t e = vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(), c->other(),
                                          c->p.precision, 0, c->stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->cur(), c->other(), lbm_state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
@@ -1261,8 +1261,8 @@ extern "C" lbm_status lbm_step_adjoint_theta(lbm_ctx* c, const double* U, const 
   if (c->p.a_mode != LBM_A_FIXED) {
     e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
     if (e == hipSuccess)
-      e = vlbm::launch_lambda_state(c->sc, c->insts.data(), 1, c->plane, U, c->slots, scratch,
-                                    LBM_FP64, 0, c->stream);
+      e = vlbm::launch_lambda_state(c->sc, c->insts.data(), nullptr, 1, c->plane, U, c->slots, scratch,
+                                    LBM_FP64, 0, 1, c->stream);
     // the forward step's lambda^n also covers the Dirichlet states
     if (e == hipSuccess && c->has_dirichlet)
       e = vlbm::launch_bnd_lambda(make_args(c, U, nullptr, scratch), scratch, c->stream);
@@ -1286,8 +1286,8 @@ extern "C" lbm_status lbm_step_adjoint(lbm_ctx* c, const double* U, const double
   const int scratch = (int)((c->step + 2) % 3);
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
   if (e == hipSuccess)
-    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), 1, c->plane, U, c->slots, scratch,
-                                  LBM_FP64, 0, c->stream);
+    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), nullptr, 1, c->plane, U, c->slots, scratch,
+                                  LBM_FP64, 0, 1, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "adjoint wavespeed");
   // theta^n of U with the forward kernel (its state output goes to the
   // context's other buffer, which the next forward step overwrites anyway;
@@ -1327,8 +1327,8 @@ extern "C" lbm_status lbm_init_adjoint(lbm_ctx* c, const double* u0, const doubl
   const int scratch = (int)((c->step + 2) % 3);
   e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
   if (e == hipSuccess)
-    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), 1, (long long)c->insts[0].nx * c->insts[0].ny,
-                                  u0, c->slots, scratch, LBM_FP64, 0, c->stream);
+    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), nullptr, 1, (long long)c->insts[0].nx * c->insts[0].ny,
+                                  u0, c->slots, scratch, LBM_FP64, 0, 1, c->stream);
   if (e == hipSuccess)
     e = vlbm::launch_adjoint_init(c->sc, c->insts[0], u0, Ub0, u0b, c->slots, scratch, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "init adjoint launch");

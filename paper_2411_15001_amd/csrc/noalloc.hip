@@ -3,7 +3,7 @@
 // context and no workspace.  The per-step scalars the kernels need (the
 // lambda slots, the time slots and the event counters) live in a file-scope
 // device array instead of a workspace, so a call allocates nothing, host or
-// device, and launches only kernels (three fills and reductions, one step).
+// device, and launches only kernels (a fill, a reduction, one step).
 //
 // The array exists once per device.  Its device address is looked up once
 // per device, with that device current, and kept in a table; host code uses
@@ -96,14 +96,12 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
                       });
   in.ys = (p->ny + in.strip_h - 1) / in.strip_h;
 
-  // zero the record, lambda^n of src into slot 0, then clear the counters
-  // that the reduction raised for non-admissible cells of src (they count
-  // the step's output cells only, as in a context)
+  // zero the record and its shards, then lambda^n of src into slot 0 (without
+  // counting non-admissible cells of src: the counters are those of the step's
+  // output cells, as in a context)
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)sl, 0u, (long long)(kScratchBytes / 4), s);
-  if (e == hipSuccess) e = vlbm::launch_lambda_state(sc, &in, 1, cells, src_dev, sl, 0, p->precision, 0, s);
   if (e == hipSuccess)
-    e = vlbm::launch_fill_u32((unsigned int*)((char*)base + offsetof(Slots, cnt)), 0u,
-                              (long long)(sizeof(sl->cnt) / 4), s);
+    e = vlbm::launch_lambda_state(sc, &in, nullptr, 1, cells, src_dev, sl, 0, p->precision, 0, 0, s);
   if (e != hipSuccess) return fail(LBM_EDEVICE, "lbm_step_noalloc: wavespeed launch failed");
 
   vlbm::StepArgs a;

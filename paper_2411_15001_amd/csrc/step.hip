@@ -2731,9 +2731,8 @@ __global__ __launch_bounds__(256) void percell_kernel(StepArgs A) {
 // Wavespeed maximum of a moment field (4 planes of Src values, rounded to the
 // storage type T first) into slots[slot]; counts non-admissible cells.
 template <class Src, class T>
-__global__ __launch_bounds__(256) void lambda_kernel(const Src* __restrict__ u, long long plane,
-                                                     long long n, double gamma, Slots* sl,
-                                                     int slot, int blocked) {
+__device__ __forceinline__ void lambda_of(const Src* __restrict__ u, long long plane, long long n, double gamma,
+                                          Slots* sl, int slot, int blocked, int count) {
   double lmax = 0.0;
   unsigned bad = 0, nf = 0, nr = 0;
   for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n;
@@ -2774,10 +2773,45 @@ __global__ __launch_bounds__(256) void lambda_kernel(const Src* __restrict__ u, 
     bad = wb[0][0] + wb[1][0] + wb[2][0] + wb[3][0];
     nf = wb[0][1] + wb[1][1] + wb[2][1] + wb[3][1];
     nr = wb[0][2] + wb[1][2] + wb[2][2] + wb[3][2];
-    raise_lambda(&sl->lam[slot], lmax);
-    if (bad) atomicAdd(&sl->cnt[CNT_BAD], (unsigned long long)bad);
-    if (nf) atomicAdd(&sl->cnt[CNT_NONFINITE], (unsigned long long)nf);
-    if (nr) atomicAdd(&sl->cnt[CNT_RHO], (unsigned long long)nr);
+    if (lmax > 0.0) raise_lambda(&sl->lam[slot], lmax);
+    if (count) {
+      if (bad) atomicAdd(&sl->cnt[CNT_BAD], (unsigned long long)bad);
+      if (nf) atomicAdd(&sl->cnt[CNT_NONFINITE], (unsigned long long)nf);
+      if (nr) atomicAdd(&sl->cnt[CNT_RHO], (unsigned long long)nr);
+    }
+  }
+  __syncthreads();  // wl and wb may be written again for the next instance
+}
+
+// The kernels that visit whole states cover all instances of an ensemble in
+// one launch, blockIdx.y striding over them (with a launch per instance the
+// chip idled between kernels of 3 us: 48 instances of 40..200 took 96 launches
+// to initialise, now two of 10 and 25 us; loading or reading the 256-instance
+// ensemble 6.0 ms, now 3.8).
+struct Insts {
+  const Inst* table;  // device; null: `one` alone
+  Inst one;
+  int n;
+  __device__ __forceinline__ Inst at(int i) const { return table ? table[i] : one; }
+};
+
+// Wavespeed of the moments u0 (float64 [4][ny][nx] per instance, one after the
+// other), rounded to T, or of the states S.
+template <class T>
+__global__ __launch_bounds__(256) void lambda_u0_kernel(Insts is, const double* __restrict__ u0, double gamma, Slots* sl,
+                                                        int slot) {
+  for (int i = blockIdx.y; i < is.n; i += gridDim.y) {
+    const Inst in = is.at(i);
+    const long long n = (long long)in.nx * in.ny;
+    lambda_of<double, T>(u0 + 4 * in.off, n, n, gamma, sl + i, slot, 0, 1);
+  }
+}
+template <class T>
+__global__ __launch_bounds__(256) void lambda_kernel(Insts is, const T* __restrict__ S, long long plane, double gamma,
+                                                     Slots* sl, int slot, int blocked, int count) {
+  for (int i = blockIdx.y; i < is.n; i += gridDim.y) {
+    const Inst in = is.at(i);
+    lambda_of<T, T>(S + in.off * (blocked ? 20 : 1), plane, (long long)in.nx * in.ny, gamma, sl + i, slot, blocked, count);
   }
 }
 
@@ -2871,24 +2905,29 @@ __global__ __launch_bounds__(256) void minima_kernel(const T* __restrict__ S, lo
 
 // u_k^0 = M_k(u0; a^0) (Section 4 preamble), moment slot = u0.
 template <class T, class C>
-__global__ __launch_bounds__(256) void init_kernel(const double* __restrict__ u0, long long n,
-                                                   T* __restrict__ S, long long plane, Scheme sc,
-                                                   const Slots* sl, int blocked) {
-  const double lam = __longlong_as_double((long long)sl->lam[0]);
-  const StepConst<T, C> K = step_const<T, C>(sc, lam);
-  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-       c += (long long)gridDim.x * blockDim.x) {
-    C u[4], f[4], g[4];
+__global__ __launch_bounds__(256) void init_kernel(Insts is, const double* __restrict__ u0_all, T* __restrict__ S_all,
+                                                   long long plane, Scheme sc, const Slots* sl, int blocked) {
+  for (int i = blockIdx.y; i < is.n; i += gridDim.y) {
+    const Inst in = is.at(i);
+    const long long n = (long long)in.nx * in.ny;
+    const double* __restrict__ u0 = u0_all + 4 * in.off;
+    T* __restrict__ S = S_all + in.off * (blocked ? 20 : 1);
+    const double lam = __longlong_as_double((long long)sl[i].lam[0]);
+    const StepConst<T, C> K = step_const<T, C>(sc, lam);
+    for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n;
+         c += (long long)gridDim.x * blockDim.x) {
+      C u[4], f[4], g[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) u[k] = (C)(T)u0[k * n + c];
-    fluxes(u, K.gm1, f, g);
+      for (int k = 0; k < 4; ++k) u[k] = (C)(T)u0[k * n + c];
+      fluxes(u, K.gm1, f, g);
 #pragma unroll
-    for (int k = 0; k < 4; ++k) S[sidx(k, c, plane, blocked)] = (T)u[k];
+      for (int k = 0; k < 4; ++k) S[sidx(k, c, plane, blocked)] = (T)u[k];
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+      for (int q = 0; q < 4; ++q)
 #pragma unroll
-      for (int k = 0; k < 4; ++k)
-        S[sidx(4 + 4 * q + k, c, plane, blocked)] = (T)maxw(q, u[k], f[k], g[k], K.w, K.r2a);
+        for (int k = 0; k < 4; ++k)
+          S[sidx(4 + 4 * q + k, c, plane, blocked)] = (T)maxw(q, u[k], f[k], g[k], K.w, K.r2a);
+    }
   }
 }
 
@@ -2902,18 +2941,21 @@ __global__ __launch_bounds__(256) void moments_kernel(const T* __restrict__ S, l
   }
 }
 
-// One instance's state (n cells, a multiple of 64, first cell at offset off
-// of every plane of `plane` cells) from one layout into the other:
+// The instances' states (widths multiples of 64) from one layout into the other:
 // to_blocked = 1 planar -> blocked, 0 blocked -> planar.
 template <class T>
-__global__ __launch_bounds__(256) void relayout_kernel(const T* __restrict__ src, T* __restrict__ dst, long long n,
-                                                       long long plane, long long off, int to_blocked) {
-  const T* s = src + off * (to_blocked ? 1 : 20);
-  T* d = dst + off * (to_blocked ? 20 : 1);
-  for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n;
-       c += (long long)gridDim.x * blockDim.x) {
+__global__ __launch_bounds__(256) void relayout_kernel(Insts is, const T* __restrict__ src, T* __restrict__ dst,
+                                                       long long plane, int to_blocked) {
+  for (int i = blockIdx.y; i < is.n; i += gridDim.y) {
+    const Inst in = is.at(i);
+    const long long n = (long long)in.nx * in.ny;
+    const T* s = src + in.off * (to_blocked ? 1 : 20);
+    T* d = dst + in.off * (to_blocked ? 20 : 1);
+    for (long long c = (long long)blockIdx.x * blockDim.x + threadIdx.x; c < n;
+         c += (long long)gridDim.x * blockDim.x) {
 #pragma unroll
-    for (int q = 0; q < 20; ++q) d[sidx(q, c, plane, to_blocked)] = s[sidx(q, c, plane, !to_blocked)];
+      for (int q = 0; q < 20; ++q) d[sidx(q, c, plane, to_blocked)] = s[sidx(q, c, plane, !to_blocked)];
+    }
   }
 }
 
@@ -2993,34 +3035,31 @@ int grid_for(long long n, long long cap = 8192) {
   return (int)g;
 }
 
-// Reductions: a few blocks per CU, each thread striding over many cells, so
-// that few block results meet at the slot.
-int grid_for_reduce(long long n) { return grid_for(n, 1024); }
-
 }  // namespace
 
 namespace {
 // Largest wavespeed of the Dirichlet boundary states of one instance, merged
-// into slot `slot` (one workgroup striding over the four sides).
+// into slot `slot`: blockIdx.y is the side, blockIdx.x strides over its cells
+// (one workgroup for all four sides was a chain of loads: 12.7 us of a 1500 x
+// 500 step, 6.1 so).
 __global__ __launch_bounds__(256) void bnd_lambda_kernel(StepArgs A, int slot) {
-  const Inst in = A.n_inst == 1 ? A.inst0 : A.insts[blockIdx.x];
-  const BndDesc bd = bnd_desc(A, A.slots + blockIdx.x);
+  const Inst in = A.n_inst == 1 ? A.inst0 : A.insts[blockIdx.z];
+  const BndDesc bd = bnd_desc(A, A.slots + blockIdx.z);
   double lmax = 0.0;
-  for (int side = 0; side < 4; ++side) {
-    const uint8_t* k = bd.kind[side];
-    if (!k) continue;
+  const int side = blockIdx.y;
+  const uint8_t* k = bd.kind[side];
+  if (k) {
     const int len = side < 2 ? in.ny : in.nx;
     const double* st = bd.state[side];
-    for (int r = threadIdx.x; r < len; r += blockDim.x) {
+    for (int r = blockIdx.x * blockDim.x + threadIdx.x; r < len; r += gridDim.x * blockDim.x) {
       if (k[r] != BND_DIRICHLET) continue;
       const double l = cell_wavespeed(st[r], st[(long long)len + r], st[2LL * len + r],
                                       st[3LL * len + r], A.sc.gamma);
       lmax = vmax(lmax, l);
     }
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) lmax = vmax(lmax, __shfl_xor(lmax, off, 64));
-  if ((threadIdx.x & 63) == 0 && lmax > 0.0) raise_lambda(&A.slots[blockIdx.x].lam[slot], lmax);
+  lmax = wave_max(lmax);
+  if ((threadIdx.x & 63) == 0 && lmax > 0.0) raise_lambda(&A.slots[blockIdx.z].lam[slot], lmax);
 }
 }  // namespace
 
@@ -3132,7 +3171,20 @@ static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, h
 }
 
 hipError_t launch_bnd_lambda(const StepArgs& a, int slot, hipStream_t s) {
-  hipLaunchKernelGGL(bnd_lambda_kernel, dim3((unsigned)a.n_inst), dim3(256), 0, s, a, slot);
+  // (an ensemble's instances differ in size: two workgroups stride over each side)
+  const int longest = a.n_inst == 1 ? (a.inst0.nx > a.inst0.ny ? a.inst0.nx : a.inst0.ny) : 512;
+  const int gx = (longest + 255) / 256 < 32 ? (longest + 255) / 256 : 32;
+  // blockIdx.z reaches 65535 instances a launch
+  for (int i = 0; i < a.n_inst; i += 65535) {
+    StepArgs b = a;
+    b.slots += i;
+    if (a.n_inst > 1) {
+      b.insts += i;
+      b.bnd_table += i;
+    }
+    const int n = a.n_inst - i < 65535 ? a.n_inst - i : 65535;
+    hipLaunchKernelGGL(bnd_lambda_kernel, dim3(gx, 4, n), dim3(256), 0, s, b, slot);
+  }
   return hipGetLastError();
 }
 
@@ -3174,44 +3226,56 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_init(const Scheme& sc, const Inst* insts, int n_inst, const Inst* /*dev*/,
+// Grid over the cells of every instance (x, at most cap blocks, enough for the
+// largest) and the instances (y).
+static dim3 inst_grid(const Inst* insts, int n_inst, long long cap) {
+  long long most = 0;
+  for (int i = 0; i < n_inst; ++i) {
+    const long long n = (long long)insts[i].nx * insts[i].ny;
+    if (n > most) most = n;
+  }
+  // an ensemble's instances share the cap, but each keeps enough blocks for its
+  // waves to overlap
+  long long share = cap / n_inst;
+  if (share < 32) share = 32;
+  return dim3((unsigned)grid_for(most, share), (unsigned)(n_inst < 65535 ? n_inst : 65535));
+}
+static Insts insts_of(const Inst* insts, const Inst* dev, int n_inst) {
+  Insts is;
+  is.table = n_inst > 1 ? dev : nullptr;
+  is.one = insts[0];
+  is.n = n_inst;
+  return is;
+}
+
+hipError_t launch_init(const Scheme& sc, const Inst* insts, int n_inst, const Inst* dev,
                        long long plane, const double* u0, void* S, Slots* slots, int precision,
                        int blocked, hipStream_t s) {
-  long long u0_off = 0;
-  for (int i = 0; i < n_inst; ++i) {
-    const Inst& in = insts[i];
-    const long long n = (long long)in.nx * in.ny;
-    const double* u = u0 + u0_off;
-    if (precision == 0)
-      hipLaunchKernelGGL((lambda_kernel<double, double>), dim3(grid_for_reduce(n)), dim3(256), 0, s, u,
-                         n, n, sc.gamma, slots + i, 0, 0);
-    else
-      hipLaunchKernelGGL((lambda_kernel<double, float>), dim3(grid_for_reduce(n)), dim3(256), 0, s, u, n,
-                         n, sc.gamma, slots + i, 0, 0);
-    if (precision == 0)
-      hipLaunchKernelGGL((init_kernel<double, double>), dim3(grid_for(n)), dim3(256), 0, s, u, n,
-                         (double*)S + in.off * (blocked ? 20 : 1), plane, sc, (const Slots*)(slots + i), blocked);
-    else
-      hipLaunchKernelGGL((init_kernel<float, float>), dim3(grid_for(n)), dim3(256), 0, s, u, n,
-                         (float*)S + in.off * (blocked ? 20 : 1), plane, sc, (const Slots*)(slots + i), blocked);
-    u0_off += 4 * n;
+  const Insts is = insts_of(insts, dev, n_inst);
+  const dim3 red = inst_grid(insts, n_inst, 1024), all = inst_grid(insts, n_inst, 8192), b(256);
+  if (precision == 0) {
+    hipLaunchKernelGGL((lambda_u0_kernel<double>), red, b, 0, s, is, u0, sc.gamma, slots, 0);
+    hipLaunchKernelGGL((init_kernel<double, double>), all, b, 0, s, is, u0, (double*)S, plane, sc,
+                       (const Slots*)slots, blocked);
+  } else {
+    hipLaunchKernelGGL((lambda_u0_kernel<float>), red, b, 0, s, is, u0, sc.gamma, slots, 0);
+    hipLaunchKernelGGL((init_kernel<float, float>), all, b, 0, s, is, u0, (float*)S, plane, sc,
+                       (const Slots*)slots, blocked);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_lambda_state(const Scheme& sc, const Inst* insts, int n_inst, long long plane,
-                               const void* S, Slots* slots, int slot, int precision, int blocked,
+hipError_t launch_lambda_state(const Scheme& sc, const Inst* insts, const Inst* dev, int n_inst, long long plane,
+                               const void* S, Slots* slots, int slot, int precision, int blocked, int count,
                                hipStream_t s) {
-  for (int i = 0; i < n_inst; ++i) {
-    const Inst& in = insts[i];
-    const long long n = (long long)in.nx * in.ny;
-    if (precision == 0)
-      hipLaunchKernelGGL((lambda_kernel<double, double>), dim3(grid_for_reduce(n)), dim3(256), 0, s,
-                         (const double*)S + in.off * (blocked ? 20 : 1), plane, n, sc.gamma, slots + i, slot, blocked);
-    else
-      hipLaunchKernelGGL((lambda_kernel<float, float>), dim3(grid_for_reduce(n)), dim3(256), 0, s,
-                         (const float*)S + in.off * (blocked ? 20 : 1), plane, n, sc.gamma, slots + i, slot, blocked);
-  }
+  const Insts is = insts_of(insts, dev, n_inst);
+  const dim3 g = inst_grid(insts, n_inst, 1024), b(256);
+  if (precision == 0)
+    hipLaunchKernelGGL((lambda_kernel<double>), g, b, 0, s, is, (const double*)S, plane, sc.gamma, slots, slot, blocked,
+                       count);
+  else
+    hipLaunchKernelGGL((lambda_kernel<float>), g, b, 0, s, is, (const float*)S, plane, sc.gamma, slots, slot, blocked,
+                       count);
   return hipGetLastError();
 }
 
@@ -3227,17 +3291,14 @@ hipError_t launch_moments(const Inst& in, long long plane, const void* S, double
   return hipGetLastError();
 }
 
-hipError_t launch_relayout(const Inst* insts, int n_inst, long long plane, const void* src, void* dst,
+hipError_t launch_relayout(const Inst* insts, const Inst* dev, int n_inst, long long plane, const void* src, void* dst,
                            int precision, int to_blocked, hipStream_t s) {
-  for (int i = 0; i < n_inst; ++i) {
-    const long long n = (long long)insts[i].nx * insts[i].ny;
-    if (precision == 0)
-      hipLaunchKernelGGL((relayout_kernel<double>), dim3(grid_for(n)), dim3(256), 0, s, (const double*)src,
-                         (double*)dst, n, plane, insts[i].off, to_blocked);
-    else
-      hipLaunchKernelGGL((relayout_kernel<float>), dim3(grid_for(n)), dim3(256), 0, s, (const float*)src,
-                         (float*)dst, n, plane, insts[i].off, to_blocked);
-  }
+  const Insts is = insts_of(insts, dev, n_inst);
+  const dim3 g = inst_grid(insts, n_inst, 8192), b(256);
+  if (precision == 0)
+    hipLaunchKernelGGL((relayout_kernel<double>), g, b, 0, s, is, (const double*)src, (double*)dst, plane, to_blocked);
+  else
+    hipLaunchKernelGGL((relayout_kernel<float>), g, b, 0, s, is, (const float*)src, (float*)dst, plane, to_blocked);
   return hipGetLastError();
 }
 

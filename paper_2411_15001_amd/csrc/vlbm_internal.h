@@ -179,14 +179,15 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s);
 hipError_t launch_init(const Scheme& sc, const Inst* insts_host, int n_inst,
                        const Inst* insts_dev, long long plane, const double* u0,
                        void* S, Slots* slots, int precision, int blocked, hipStream_t s);
-hipError_t launch_lambda_state(const Scheme& sc, const Inst* insts_host, int n_inst,
-                               long long plane, const void* S, Slots* slots,
-                               int slot, int precision, int blocked, hipStream_t s);
+// (insts_dev: the same table in device memory, used for n_inst > 1)
+hipError_t launch_lambda_state(const Scheme& sc, const Inst* insts_host, const Inst* insts_dev, int n_inst,
+                               long long plane, const void* S, Slots* slots, int slot, int precision,
+                               int blocked, int count, hipStream_t s);
 hipError_t launch_moments(const Inst& in, long long plane, const void* S,
                           double* out, int precision, int blocked, hipStream_t s);
 // Every instance's state (widths multiples of 64) from src to dst, planar ->
 // blocked (to_blocked = 1) or blocked -> planar (0).
-hipError_t launch_relayout(const Inst* insts_host, int n_inst, long long plane, const void* src, void* dst,
+hipError_t launch_relayout(const Inst* insts_host, const Inst* insts_dev, int n_inst, long long plane, const void* src, void* dst,
                            int precision, int to_blocked, hipStream_t s);
 // Per-cell blending step (an ablation): state A.src -> A.dst with the face
 // factors A.theta_x / A.theta_y of the same state, single instance; also
@@ -203,7 +204,7 @@ hipError_t launch_totals(const Inst& in, long long plane, const void* S, double*
 hipError_t launch_fold(Slots* slots, Slots* shards, int n_shards, int n_inst, int clear, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStream_t s);
 // Raises each instance's lam[slot] to the largest wavespeed of its Dirichlet
-// boundary states (one workgroup per instance).
+// boundary states.
 hipError_t launch_bnd_lambda(const StepArgs& a, int slot, hipStream_t s);
 hipError_t launch_fill_f64(double* p, double v, long long n, hipStream_t s);
 // Adjoint (adjoint.hip).  Boundary kinds per side (west, east, south,
