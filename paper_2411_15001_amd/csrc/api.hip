@@ -91,7 +91,7 @@ Scheme make_scheme(const lbm_params* p) {
 }
 
 struct Layout {
-  size_t slots, shards, slots_save, red, insts, items, bndt, bufA, bufB, theta, total;
+  size_t slots, shards, red, slots_save, insts, items, bndt, bufA, bufB, theta, total;
 };
 
 Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
@@ -107,10 +107,10 @@ Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
   o = align_up(o + sizeof(Slots) * (size_t)n);
   L.shards = o;  // see Slots
   o = align_up(o + sizeof(Slots) * (size_t)n * vlbm::kShards);
+  L.red = o;  // block partials of lbm_totals and lbm_diagnostics, read with a single instance's records
+  o = align_up(o + sizeof(double) * 8 * (size_t)kTotalsBlocks);
   L.slots_save = o;  // the adjoint entry points park the slots here
   o = align_up(o + sizeof(Slots));
-  L.red = o;  // block partials of lbm_totals
-  o = align_up(o + sizeof(double) * 8 * (size_t)kTotalsBlocks);
   L.insts = o;
   o = align_up(o + sizeof(Inst) * (size_t)n);
   L.items = o;
@@ -152,6 +152,9 @@ struct lbm_ctx {
   // whether steps ran since the shards were last folded; a step that the
   // caller records into a graph may be replayed at any time after (recorded)
   bool raised = false, recorded = false;
+  // every counter is zero: lbm_moments cleared them and nothing that counts
+  // was enqueued since
+  bool clean = false;
   Inst* insts_dev = nullptr;
   int* items_dev = nullptr;
   hipStream_t stream = nullptr;
@@ -409,6 +412,7 @@ bool being_recorded(lbm_ctx* c) {
 // read, and before every read once steps were recorded.
 void note_steps(lbm_ctx* c) {
   c->raised = true;
+  c->clean = false;
   if (!c->recorded) c->recorded = being_recorded(c);
 }
 
@@ -420,25 +424,31 @@ hipError_t fold_shards(lbm_ctx* c, int clear) {
   return vlbm::launch_fold(c->slots, c->shards, c->n_shards, c->n_inst, clear, c->stream);
 }
 
-// The instances' records with their shards folded in.  A single instance's
-// shards come along in the same copy (they follow its record) and are folded
+// The instances' records with their shards folded in, and (part) the first
+// n_part doubles of the reduction area.  A single instance's shards and that
+// area follow its record: one copy brings them all and the shards are folded
 // here; an ensemble's are folded on the device first.
-lbm_status read_slots(lbm_ctx* c, std::vector<Slots>& h) {
-  const bool here = c->n_inst == 1 && c->shards != c->slots;
-  const size_t skip = here ? (c->lay.shards - c->lay.slots) / sizeof(Slots) : 0;
-  h.resize(here ? skip + c->n_shards : c->n_inst);
-  hipError_t e = here ? hipSuccess : fold_shards(c, -1);
+lbm_status read_slots(lbm_ctx* c, std::vector<Slots>& h, std::vector<double>* part = nullptr, size_t n_part = 0) {
+  const bool one = c->n_inst == 1;
+  const size_t to_red = (c->lay.red - c->lay.slots) / sizeof(Slots);
+  h.resize(one ? to_red + (n_part * sizeof(double) + sizeof(Slots) - 1) / sizeof(Slots) : c->n_inst);
+  hipError_t e = one ? hipSuccess : fold_shards(c, -1);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h.data(), c->slots, sizeof(Slots) * h.size(), hipMemcpyDeviceToHost, c->stream);
+  if (part) part->resize(n_part);
+  if (e == hipSuccess && part && !one)
+    e = hipMemcpyAsync(part->data(), c->ws + c->lay.red, sizeof(double) * n_part, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reading device slots");
-  if (here) {
-    for (int i = 0; i < c->n_shards; ++i) {
+  if (one) {
+    const size_t skip = (c->lay.shards - c->lay.slots) / sizeof(Slots);
+    for (int i = 0; i < c->n_shards && c->shards != c->slots; ++i) {
       const Slots& sh = h[skip + i];
       // (bit patterns of non-negative doubles order like the integers)
       for (int k = 0; k < 3; ++k) h[0].lam[k] = std::max(h[0].lam[k], sh.lam[k]);
       for (int k = 0; k < vlbm::CNT_N; ++k) h[0].cnt[k] += sh.cnt[k];
     }
+    if (part) memcpy(part->data(), &h[to_red], sizeof(double) * n_part);
     h.resize(1);
   }
   return LBM_OK;
@@ -528,7 +538,7 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
   }
   // the records and, behind them, their shards
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)c->slots, 0u,
-                                       (long long)((c->lay.slots_save - c->lay.slots) / 4), c->stream);
+                                       (long long)((c->lay.red - c->lay.slots) / 4), c->stream);
   if (e == hipSuccess)
     e = vlbm::launch_init(c->sc, c->insts.data(), n, c->insts_dev, c->plane, u0, c->cur(),
                           c->slots, p->precision, c->blocked, c->stream);
@@ -691,6 +701,10 @@ lbm_status lbm_moments(lbm_ctx* c, int32_t inst, double* out) {
   hipError_t e = vlbm::launch_moments(c->insts[inst], c->plane, c->cur(), out, c->p.precision, c->blocked,
                                       c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "moments launch");
+  if (c->clean && !c->recorded) {  // nothing was counted since the last call cleared the counters
+    e = hipStreamSynchronize(c->stream);
+    return e == hipSuccess ? LBM_OK : hip_fail(c, e, "moments");
+  }
   std::vector<Slots> h;
   lbm_status st = read_slots(c, h);
   if (st != LBM_OK) return st;
@@ -716,17 +730,16 @@ lbm_status lbm_moments(lbm_ctx* c, int32_t inst, double* out) {
   } else if (bouchut) {
     res = fail(c, LBM_EBOUCHUT, "the fixed kinetic speed fell below the Bouchut bound");
   }
-  // every counter starts again from zero
+  // every counter starts again from zero, behind the read on the stream
   bool any = false;
-  for (auto& s : h)
-    for (int k = 0; k < vlbm::CNT_N; ++k) {
-      any |= s.cnt[k] != 0;
-      s.cnt[k] = 0;
-    }
+  for (const Slots& r : h)
+    for (int k = 0; k < vlbm::CNT_N; ++k) any |= r.cnt[k] != 0;
   if (any) {
-    st = write_slots(c, h);
-    if (st != LBM_OK) return st;
+    const long long records = c->n_inst == 1 ? (long long)((c->lay.red - c->lay.slots) / sizeof(Slots)) : c->n_inst;
+    e = vlbm::launch_clear_counts(c->slots, records, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "clearing the counters");
   }
+  c->clean = true;
   return res;
 }
 
@@ -738,19 +751,18 @@ lbm_status lbm_diagnostics(lbm_ctx* c, int32_t inst, lbm_diag* d) {
   // is in a caller buffer, so its minima are not available
   const Inst& in = c->insts[inst];
   const long long n = (long long)in.nx * in.ny;
-  const int blocks = (int)std::min<long long>((n + 255) / 256, kTotalsBlocks);
+  // (few partials to read back, unless the state is large enough to need more
+  // blocks to stream it)
+  const int blocks = (int)std::min<long long>((n + 255) / 256, n > (1 << 22) ? kTotalsBlocks : 256);
   std::vector<double> part;
-  if (!c->detached) {
-    double* dp = (double*)(c->ws + c->lay.red);
-    hipError_t e = vlbm::launch_minima(in, c->plane, c->cur(), dp, blocks, c->p.precision, c->blocked,
-                                       c->stream);
-    part.resize((size_t)blocks * 2);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(part.data(), dp, sizeof(double) * part.size(), hipMemcpyDeviceToHost, c->stream);
+  const bool minima = !c->detached;
+  if (minima) {
+    hipError_t e = vlbm::launch_minima(in, c->plane, c->cur(), (double*)(c->ws + c->lay.red), blocks, c->p.precision,
+                                       c->blocked, c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "minima");
   }
   std::vector<Slots> h;
-  lbm_status st = read_slots(c, h);
+  lbm_status st = minima ? read_slots(c, h, &part, (size_t)blocks * 2) : read_slots(c, h);
   if (st != LBM_OK) return st;
   const Slots& s = h[inst];
   const int slot = (int)(c->step % 3);
@@ -842,6 +854,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
                                              c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "set_state copy");
   const int slot = (int)(c->step % 3);
+  c->clean = false;  // (non-admissible cells of the state are counted)
   if (e == hipSuccess) e = fold_shards(c, slot);
   if (e == hipSuccess)
     e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(),
@@ -1052,6 +1065,7 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
     }
   }
   std::vector<Slots> saved;
+  c->clean = false;
   lbm_status st = read_slots(c, saved);
   if (st != LBM_OK) return st;
   const int rows_c[] = {4, 8, 16, 32, 64, 128, 256};
@@ -1257,6 +1271,7 @@ extern "C" lbm_status lbm_step_adjoint_theta(lbm_ctx* c, const double* U, const 
   // a^n: fixed, or from lambda^n of U_n in the slot the next forward step
   // clears before it reads it (no other slot is touched)
   const int scratch = (int)((c->step + 2) % 3);
+  c->clean = false;  // (the reduction below counts non-admissible cells of U_n)
   hipError_t e = hipSuccess;
   if (c->p.a_mode != LBM_A_FIXED) {
     e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
@@ -1284,6 +1299,7 @@ extern "C" lbm_status lbm_step_adjoint(lbm_ctx* c, const double* U, const double
   // lambda^n of U (scratch slot: a second Slots record is not available, so
   // use the slot that the next forward step would clear)
   const int scratch = (int)((c->step + 2) % 3);
+  c->clean = false;
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
   if (e == hipSuccess)
     e = vlbm::launch_lambda_state(c->sc, c->insts.data(), nullptr, 1, c->plane, U, c->slots, scratch,

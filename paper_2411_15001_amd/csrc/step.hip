@@ -2984,6 +2984,13 @@ __global__ __launch_bounds__(64) void fold_kernel(Slots* slots, Slots* shards, i
   }
 }
 
+// Zeroes the event counters of n slot records (lambda and t stay).
+__global__ __launch_bounds__(256) void clear_counts_kernel(Slots* sl, long long n) {
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n * CNT_N;
+       i += (long long)gridDim.x * blockDim.x)
+    sl[i / CNT_N].cnt[i % CNT_N] = 0ull;
+}
+
 __global__ void fill_u32_kernel(unsigned int* p, unsigned int v, long long n) {
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (long long)gridDim.x * blockDim.x)
@@ -3335,6 +3342,11 @@ hipError_t launch_minima(const Inst& in, long long plane, const void* S, double*
   else
     hipLaunchKernelGGL((minima_kernel<float>), dim3(blocks), dim3(256), 0, s,
                        (const float*)S + in.off * (blocked ? 20 : 1), plane, n, part, blocked);
+  return hipGetLastError();
+}
+
+hipError_t launch_clear_counts(Slots* slots, long long n, hipStream_t s) {
+  hipLaunchKernelGGL(clear_counts_kernel, dim3(grid_for(n * CNT_N)), dim3(256), 0, s, slots, n);
   return hipGetLastError();
 }
 

@@ -201,6 +201,7 @@ hipError_t launch_minima(const Inst& in, long long plane, const void* S, double*
 // grid is `blocks` workgroups of 256 threads.
 hipError_t launch_totals(const Inst& in, long long plane, const void* S, double* part,
                          int blocks, int precision, int blocked, hipStream_t s);
+hipError_t launch_clear_counts(Slots* slots, long long n, hipStream_t s);
 hipError_t launch_fold(Slots* slots, Slots* shards, int n_shards, int n_inst, int clear, hipStream_t s);
 hipError_t launch_fill_u32(unsigned int* p, unsigned int v, long long n, hipStream_t s);
 // Raises each instance's lam[slot] to the largest wavespeed of its Dirichlet
