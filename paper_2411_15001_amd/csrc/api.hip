@@ -753,7 +753,7 @@ lbm_status lbm_diagnostics(lbm_ctx* c, int32_t inst, lbm_diag* d) {
   const long long n = (long long)in.nx * in.ny;
   // (few partials to read back, unless the state is large enough to need more
   // blocks to stream it)
-  const int blocks = (int)std::min<long long>((n + 255) / 256, n > (1 << 22) ? kTotalsBlocks : 256);
+  const int blocks = (int)std::min<long long>((n + 255) / 256, n > (1 << 22) ? kTotalsBlocks : 512);
   std::vector<double> part;
   const bool minima = !c->detached;
   if (minima) {
