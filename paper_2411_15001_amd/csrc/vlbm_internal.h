@@ -152,9 +152,9 @@ inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, 
 template <class Strips>
 int march_rows(int precision, bool lmp, const Strips& strips) {
   const double slots = precision == 0 ? 1024.0 : 2048.0;
-  const double c = lmp ? 0.44 : (precision == 0 ? 0.54 : 0.58);
-  const double e = precision == 0 ? (lmp ? 1.5 : 0.75) : (lmp ? 0.75 : 0.5);
-  const double g = precision != 0 && !lmp ? 0.001 : 0.0;
+  const double c = lmp ? 0.44 : (precision == 0 ? 0.54 : 0.48);
+  const double e = precision == 0 ? (lmp ? 1.5 : 0.75) : (lmp ? 0.75 : 0.4);
+  const double g = precision != 0 && !lmp ? 0.004 : 0.0;
   int best = 4;
   double least = 0.0;
   for (int h : {4, 8, 12, 16, 24, 32, 48, 64}) {
