@@ -2510,7 +2510,7 @@ void step_kernel(StepArgs A) {
 // chain of loads (some 20 us against 8), come first and go round the XCDs; the
 // others follow in one contiguous range for each XCD.  In the plain order those
 // of the last row came last and set the launch's end: 1500 x 500 float64 RLMP
-// 94 us a step, 84 so; 2000^2 LMP 445 / 434.  (Used in float64 under density
+// 94 us a step, 84 so (77 with the limiter set fixed at compile time); 2000^2 LMP 445 / 434.  (Used in float64 under density
 // bounds, where two waves share a SIMD; with three or four the plain order
 // measured 1-10% faster.)
 // block: of `groups` (a multiple of 8, at least X Y); ys = Y for none.
@@ -3075,6 +3075,11 @@ __global__ void fill_f64_kernel(double* p, double v, long long n) {
 #ifndef VLBM_WPE_ROW_F32_LMP
 #define VLBM_WPE_ROW_F32_LMP 4
 #endif
+// With boundary descriptions the float32 bounds-limited form needs 145 (four
+// waves: 18 spilled, 2000^2 LMP 292 us a step; three 266, 400^2 28.7 / 27.3).
+#ifndef VLBM_WPE_ROW_F32_LMP_BND
+#define VLBM_WPE_ROW_F32_LMP_BND 3
+#endif
 
 int grid_for(long long n, long long cap = 8192) {
   long long g = (n + 255) / 256;
@@ -3143,8 +3148,10 @@ static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) 
 }
 
 // Launch of the row kernel (a.rows).  The variants are those of the marches:
-// the limiter set fixed at compile time for the sets with PP and pressure, the
-// rest and boundary descriptions with the set read at run time.
+// the limiter set fixed at compile time for the sets with PP and pressure, with
+// boundary descriptions too, the rest with the set read at run time.  (Read at
+// run time, boundary descriptions: 1500 x 500 float64 RLMP 80 us a step, fixed
+// 76; 2000^2 451 / 438; PP 1500 x 500 49.5 / 47; float32 PP 1000^2 56.6 / 55.)
 template <class T, bool LMP, int WPE, bool BLK, bool LATE = false>
 static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
@@ -3152,7 +3159,13 @@ static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
   const dim3 block(64 * kRowsPerGroup);
   if constexpr (!BLK && !LATE) {
     if (a.bnd) {
-      hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, true, false>), grid, block, 0, s, a);
+      constexpr int kWaves = LMP && sizeof(T) == 4 ? VLBM_WPE_ROW_F32_LMP_BND : WPE;
+      if (lims == kFixed && !a.theta_x)
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, kFixed, false, true, false>), grid, block, 0, s, a);
+      else if (LMP && lims == kRelaxed && !a.theta_x)
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, LMP ? kRelaxed : 0, false, true, false>), grid, block, 0, s, a);
+      else
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, 0, false, true, false>), grid, block, 0, s, a);
       return;
     }
   }

@@ -144,7 +144,7 @@ inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, 
 // below a fraction c of a full one, since a lone wave's chain of rows takes
 // that long.  c, e and g are fitted to 240 timings (15 grids of 960^2 to
 // 8192^2 and 4 : 1, strips of 4 to 64 rows, the four classes): the height
-// chosen is within 1.1% of the best on average, 13% at worst.  The tallest
+// chosen is within 0.7% of the best on average, 13% at worst.  The tallest
 // strips that fill one round, the rule before, left a nearly empty second
 // round where a little more than one was needed: 1536^2 float64 PP 215 us a
 // step with strips of 32 rows (1.13 rounds), 161 with 12 (3 rounds); 3072^2

@@ -93,6 +93,25 @@ def test_rows_equal_marches_with_described_boundaries(nx, ny, lims, prec, gpu):
         check(run(u0, kw, None, bnd=sides), run(u0, kw, (4, 1), bnd=sides), gpu)
 
 
+@pytest.mark.parametrize("nx,ny", [(3, 2), (130, 6), (257, 30)])
+@pytest.mark.parametrize("lims,sponge", [(11, 0), (9, 2), (11, 2), (13, 2), (15, 0), (2, 0)])
+@pytest.mark.parametrize("prec", [0, 1])
+def test_described_boundaries_with_the_limiter_set_fixed_or_read(nx, ny, lims, sponge, prec, gpu):
+    """The sets with PP and pressure are fixed at compile time unless a sponge
+    or another set asks for the general form."""
+    print("bnd limiters", nx, ny, lims, sponge, prec, flush=True)
+    rng = np.random.default_rng(5)
+    bnd = {}
+    for side in range(4):
+        n = ny if side < 2 else nx
+        st = cases.prim_to_cons(rng.uniform(0.5, 1.5, n), rng.uniform(-1, 1, n), rng.uniform(-1, 1, n),
+                                rng.uniform(0.5, 1.5, n), 1.4)
+        bnd[side] = (rng.integers(0, 3, n).astype(np.uint8), st)
+    kw = dict(limiters=lims, a_beta=1.1, bc_x=1, bc_y=1, sponge=sponge, precision=prec)
+    u0 = field(nx, ny, 12)
+    check(run(u0, kw, None, bnd=bnd), run(u0, kw, (4, 1), bnd=bnd), gpu)
+
+
 @pytest.mark.parametrize("sides", [[(40, 41), (64, 3), (129, 70), (1, 1)], [(64, 64), (128, 5), (192, 130)]])
 @pytest.mark.parametrize("lims", [9, 11])
 def test_rows_of_an_ensemble_equal_marches(sides, lims, gpu):
