@@ -176,6 +176,7 @@ struct lbm_ctx {
   // marches.  Caller buffers (lbm_get_state, lbm_set_state,
   // lbm_step_between, the adjoint) are planar; the library converts.
   int blocked = 0;
+  int ragged = 0;  // some row of the planar layout starts off 16 elements
   // boundary descriptions per instance (caller-owned device arrays; copied
   // to the workspace table for ensembles); per instance and side: any
   // Dirichlet cell
@@ -353,6 +354,7 @@ vlbm::StepArgs make_args(const lbm_ctx* c, const void* src, void* dst, int slot)
   a.xcd_remap = c->xcd;
   a.groups = compute_groups(c);
   a.rows = c->rows;
+  a.ragged = c->ragged;
   a.sc = c->sc;
   if (c->n_inst > 1)
     a.bnd_table = (const vlbm::BndDesc*)(c->ws + c->lay.bndt);
@@ -522,6 +524,8 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
     off += (long long)nx[i] * ny[i];
   }
   c->plane = off;
+  for (const Inst& in : c->insts)
+    if (!vlbm::even_rows(in, c->plane)) c->ragged = 1;
   {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&

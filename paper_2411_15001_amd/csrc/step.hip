@@ -230,10 +230,16 @@ __device__ __forceinline__ double face_theta(const Scheme& s, const C us[4], con
 // Store of the new state.  With the float32 state the stores bypass cache
 // allocation (non-temporal): the state is written once and read by the next
 // launch from HBM anyway, and this measured 2% faster on the 8192^2 blast;
-// with float64 it measured 3% slower, so plain stores are kept there.
-template <class T>
+// with float64 it measured 3% slower, so plain stores are kept there.  Past
+// the caches a wave's 256 bytes cost a read-modify-write at each end that does
+// not meet a line, so rows that start anywhere (NT = false, StepArgs::ragged)
+// are stored through L2, where the neighbouring strip completes the line.  us a
+// step, float32 state, non-temporal / through L2: 2001 x 2047 PP 208 / 171, LMP
+// 247 / 190; 4001^2 805 / 617, 934 / 727; 1000 x 1001 PP 50 / 40; 801 x 799
+// 35 / 27; with rows on 64 bytes 4000^2 PP 538 / 554, 2000 x 2048 164 / 167.
+template <bool NT = true, class T>
 __device__ __forceinline__ void put(T* p, T v) {
-  if constexpr (sizeof(T) == 4)
+  if constexpr (NT && sizeof(T) == 4)
     __builtin_nontemporal_store(v, p);
   else
     *p = v;
@@ -245,14 +251,15 @@ __device__ __forceinline__ void put(T* p, T v) {
 // (columns past the instance's edge, which pass 0xFFFFFFFF) and every lane
 // when bytes = 0 (a row the strip does not produce).  The store is thus issued on every path, and the
 // wait for the next prefetched row, which the compiler otherwise extends over
-// stores issued under a condition, leaves these in flight.  Non-temporal, as
-// put() with the float32 state.  Used by the short march with the float32
+// stores issued under a condition, leaves these in flight.  Non-temporal where
+// put() is.  Used by the short march with the float32
 // state (0.6% faster on the 8192^2 blast, 1.3% on the 256-instance ensemble;
 // with float64, and in the bounds-limited march, it measured slower).
 constexpr int kRsrcWord3 = 0x00020000;  // 32-bit data format, raw access
+template <bool NT>
 __device__ __forceinline__ void put_row(float* row, unsigned bytes, unsigned voff, float v) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(row, (short)0, (int)bytes, kRsrcWord3);
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, 0, 2);
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), r, voff, 0, NT ? 2 : 0);
 }
 
 // Raise lambda slot `slot` to at least lmax (>= 0; the bit patterns of
@@ -545,7 +552,7 @@ __device__ void bnd_cell(const StepArgs& A, const BndDesc& bd, const Inst& in, c
 // face evaluation per row).  The strip to the west evaluates that same face
 // with the same inputs and code, so both cells of a strip-edge face see the
 // same theta.
-template <class T, class C, int LIMS, bool TH, bool BND>
+template <class T, class C, int LIMS, bool TH, bool BND, bool NT>
 __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                             int ys, int lane) {
   const Scheme& sc = A.sc;
@@ -744,11 +751,11 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
         // columns past the edge get an offset beyond any row (4 gi itself
         // could wrap around 2^32 when nx is close to 2^30)
         const unsigned voff = lane_out ? (unsigned)gi * 4u : 0xFFFFFFFFu;
-        put_row(dbase + (4 + c) * P + r0, rb0, voff, (T)u1n);
-        put_row(dbase + (8 + c) * P + r0, rb0, voff, (T)u2n);
-        put_row(dbase + (12 + c) * P + r0, rb0, voff, (T)u3n);
-        put_row(dbase + c * P + r1, rb1, voff, (T)fin[c]);
-        put_row(dbase + (16 + c) * P + r1, rb1, voff, (T)u4n);
+        put_row<NT>(dbase + (4 + c) * P + r0, rb0, voff, (T)u1n);
+        put_row<NT>(dbase + (8 + c) * P + r0, rb0, voff, (T)u2n);
+        put_row<NT>(dbase + (12 + c) * P + r0, rb0, voff, (T)u3n);
+        put_row<NT>(dbase + c * P + r1, rb1, voff, (T)fin[c]);
+        put_row<NT>(dbase + (16 + c) * P + r1, rb1, voff, (T)u4n);
       } else {
         if (row0 && lane_out) {
           const unsigned o = (unsigned)L * unx + (unsigned)gi;
@@ -806,7 +813,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
 // rho, m_1 of x0 + 65.  From them each evaluates the bounds of its halo cell,
 // and lane 0 the west edge face x0 - 1/2, with the same expressions as every
 // other lane, so both strips beside an edge face see the same theta.
-template <class T, class C, int LIMS, bool TH, bool BND>
+template <class T, class C, int LIMS, bool TH, bool BND, bool NT>
 __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                           int ys, int lane) {
   const Scheme& sc = A.sc;
@@ -1091,14 +1098,14 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int
       } else {
         if (row1 && lane_out) {
           const unsigned o = (unsigned)(L - 1) * unx + (unsigned)gi;
-          put(&(dbase + (4 + c) * P)[o], (T)u1n);
-          put(&(dbase + (8 + c) * P)[o], (T)u2n);
-          put(&(dbase + (12 + c) * P)[o], (T)u3n);
+          put<NT>(&(dbase + (4 + c) * P)[o], (T)u1n);
+          put<NT>(&(dbase + (8 + c) * P)[o], (T)u2n);
+          put<NT>(&(dbase + (12 + c) * P)[o], (T)u3n);
         }
         if (row2 && lane_out) {
           const unsigned o = (unsigned)(L - 2) * unx + (unsigned)gi;
-          put(&(dbase + c * P)[o], (T)fin[c]);
-          put(&(dbase + (16 + c) * P)[o], (T)u4n);
+          put<NT>(&(dbase + c * P)[o], (T)fin[c]);
+          put<NT>(&(dbase + (16 + c) * P)[o], (T)u4n);
         }
       }
       qP[c] = s;
@@ -1866,7 +1873,7 @@ __device__ __forceinline__ RowEvents row_events(const Scheme& sc, const C (&fin)
 // bounds it: at 64^2 a wave lives 7 us, of which 3 wait for the first loads and
 // the kernel's code and 2 issue its 1035 vector instructions; at 512^2
 // (float64, PP, 4 rows per SIMD, 3 resident) 20 us a step, 7.3 of them vector issue.
-template <class T, class C, bool LMP, int LIMS, bool TH, bool BND, bool BLK>
+template <class T, class C, bool LMP, int LIMS, bool TH, bool BND, bool BLK, bool NT>
 __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in, int ii, int xs, int j, int lane,
                                               const Slots* shard) {
   const Scheme& sc = A.sc;
@@ -2012,7 +2019,7 @@ __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in,
     if constexpr (BLK)
       put(dbase + ((long long)j * nx + x0) * 20 + q * 64 + lane, (T)v);
     else
-      put(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
+      put<NT>(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
   };
   unsigned n_guard = 0, n_lim = 0;
 
@@ -2466,8 +2473,9 @@ __device__ __forceinline__ RowEvents step_row_late(const StepArgs& A, const Inst
 // whether the face factors are written (with LIMS = 0 they are written
 // whenever A.theta_x is set), BND whether boundary descriptions are read
 // (only with LIMS = 0), DMA the LDS-staged marches, BLK the blocked state
-// layout (with DMA only).
-template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool DMA = false, bool BLK = false>
+// layout (with DMA only), NT how the float32 state is stored (see put).
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool DMA = false, bool BLK = false,
+          bool NT = true>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void step_kernel(StepArgs A) {
   const int lane = threadIdx.x & 63;
@@ -2497,11 +2505,11 @@ void step_kernel(StepArgs A) {
     if constexpr (LMP && DMA)
       march_lmp_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
     else if constexpr (LMP)
-      march_lmp<T, C, LIMS, TH, BND>(A, in, ii, item, xs, ys, lane);
+      march_lmp<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
     else if constexpr (DMA)
       march_short_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
     else
-      march_short<T, C, LIMS, TH, BND>(A, in, ii, item, xs, ys, lane);
+      march_short<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
   }
 }
 
@@ -2542,7 +2550,7 @@ __device__ __forceinline__ void edges_first(int X, int Y, int groups, int block,
 
 // The row kernel: a workgroup of four waves takes four rows of a strip, one
 // row per wave (the strip table is built for strips of four rows).
-template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK, bool LATE = false>
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK, bool LATE = false, bool NT = true>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
 void row_kernel(StepArgs A) {
   const int lane = threadIdx.x & 63;
@@ -2575,7 +2583,7 @@ void row_kernel(StepArgs A) {
     if constexpr (LATE)
       ev = step_row_late<LIMS, TH, BLK>(A, in, ii, xs, j, lane, shard);
     else
-      ev = step_row<T, C, LMP, LIMS, TH, BND, BLK>(A, in, ii, xs, j, lane, shard);
+      ev = step_row<T, C, LMP, LIMS, TH, BND, BLK, NT>(A, in, ii, xs, j, lane, shard);
   }
   // one update of the slot and the counters per workgroup (every wave reaches
   // the barrier): same-address atomics of many short waves would queue
@@ -3152,7 +3160,7 @@ static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) 
 // boundary descriptions too, the rest with the set read at run time.  (Read at
 // run time, boundary descriptions: 1500 x 500 float64 RLMP 80 us a step, fixed
 // 76; 2000^2 451 / 438; PP 1500 x 500 49.5 / 47; float32 PP 1000^2 56.6 / 55.)
-template <class T, bool LMP, int WPE, bool BLK, bool LATE = false>
+template <class T, bool LMP, int WPE, bool BLK, bool LATE = false, bool NT = true>
 static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
   constexpr int kRelaxed = 1 | 4 | 8;
@@ -3161,27 +3169,27 @@ static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
     if (a.bnd) {
       constexpr int kWaves = LMP && sizeof(T) == 4 ? VLBM_WPE_ROW_F32_LMP_BND : WPE;
       if (lims == kFixed && !a.theta_x)
-        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, kFixed, false, true, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, kFixed, false, true, false, false, NT>), grid, block, 0, s, a);
       else if (LMP && lims == kRelaxed && !a.theta_x)
-        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, LMP ? kRelaxed : 0, false, true, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, LMP ? kRelaxed : 0, false, true, false, false, NT>), grid, block, 0, s, a);
       else
-        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, 0, false, true, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((row_kernel<T, T, LMP, kWaves, 0, false, true, false, false, NT>), grid, block, 0, s, a);
       return;
     }
   }
   if (lims == kFixed && a.theta_x)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, true, false, BLK, LATE>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, true, false, BLK, LATE, NT>), grid, block, 0, s, a);
   else if (lims == kFixed)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, false, false, BLK, LATE>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, kFixed, false, false, BLK, LATE, NT>), grid, block, 0, s, a);
   else if (LMP && lims == kRelaxed && !a.theta_x)
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, LMP ? kRelaxed : 0, false, false, BLK, LATE>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, LMP ? kRelaxed : 0, false, false, BLK, LATE, NT>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, false, BLK, LATE>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((row_kernel<T, T, LMP, WPE, 0, false, false, BLK, LATE, NT>), grid, block, 0, s, a);
 }
 
 static bool dma_ok(const StepArgs& a) { return a.n_inst == 1 && a.inst0.nx % 64 == 0 && !a.bnd; }
 
-template <class T, bool LMP, int WPE>
+template <class T, bool LMP, int WPE, bool NT = true>
 static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
   constexpr int kRelaxed = 1 | 4 | 8;  // (bounds-limited sets only)
@@ -3222,13 +3230,13 @@ static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, h
     }
   }
   if (a.bnd)
-    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, 0, false, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, 0, false, true, false, false, NT>), grid, block, 0, s, a);
   else if (lims == kFixed && a.theta_x)
-    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, kFixed, true, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, kFixed, true, false, false, false, NT>), grid, block, 0, s, a);
   else if (lims == kFixed)
-    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, kFixed, false, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, kFixed, false, false, false, false, NT>), grid, block, 0, s, a);
   else
-    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, 0, false, false>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((step_kernel<T, T, LMP, WPE, 0, false, false, false, false, NT>), grid, block, 0, s, a);
 }
 
 hipError_t launch_bnd_lambda(const StepArgs& a, int slot, hipStream_t s) {
@@ -3267,9 +3275,11 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
                 : launch_rows<double, false, VLBM_WPE_ROW_F64, false>(a, lims, grid, s);
     else if (lmp)
       a.blocked ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, true>(a, lims, grid, s)
+      : a.ragged  ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false, false, false>(a, lims, grid, s)
                 : launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false>(a, lims, grid, s);
     else
       a.blocked ? launch_rows<float, false, VLBM_WPE_ROW_F32, true>(a, lims, grid, s)
+      : a.ragged  ? launch_rows<float, false, VLBM_WPE_ROW_F32, false, false, false>(a, lims, grid, s)
                 : launch_rows<float, false, VLBM_WPE_ROW_F32, false>(a, lims, grid, s);
     return hipGetLastError();
   }
@@ -3280,9 +3290,11 @@ hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
       launch_step_as<double, false, VLBM_WPE_F64>(a, lims, grid, block, s);
   } else {
     if (lmp)
-      launch_step_as<float, true, VLBM_WPE_F32_LMP>(a, lims, grid, block, s);
+      a.ragged ? launch_step_as<float, true, VLBM_WPE_F32_LMP, false>(a, lims, grid, block, s)
+               : launch_step_as<float, true, VLBM_WPE_F32_LMP>(a, lims, grid, block, s);
     else
-      launch_step_as<float, false, VLBM_WPE_F32>(a, lims, grid, block, s);
+      a.ragged ? launch_step_as<float, false, VLBM_WPE_F32, false>(a, lims, grid, block, s)
+               : launch_step_as<float, false, VLBM_WPE_F32>(a, lims, grid, block, s);
   }
   return hipGetLastError();
 }

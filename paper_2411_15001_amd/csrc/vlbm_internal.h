@@ -104,11 +104,17 @@ struct StepArgs {
   int blocked;            // src and dst hold the blocked layout (a context's own
                           // buffers; every width a multiple of 64, no boundary
                           // descriptions), else planar
+  int ragged;             // some row of the planar layout does not start on a
+                          // multiple of 16 elements (64 bytes of float32)
   int rows;               // 1: the row kernel (one row of a strip per wave; the
                           // strips are kRowsPerGroup rows high and groups counts
                           // them), 0: the marches
   Scheme sc;
 };
+
+// Whether an instance's rows in the planar layout start on multiples of 16
+// elements only.
+inline bool even_rows(const Inst& in, long long plane) { return ((in.nx | in.off | plane) & 15) == 0; }
 
 // Rows of a strip that one workgroup of the row kernel takes, one per wave.
 constexpr int kRowsPerGroup = 4;

@@ -177,3 +177,24 @@ def test_autotuned_choice_keeps_the_results(gpu, tmp_path):
         tx, ty = s.step_theta()
         check((s.get_state(), tx, ty, s.diagnostics()), ref, gpu)
         s.close()
+
+
+@pytest.mark.parametrize("sides", [[(48, 5), (80, 6)], [(48, 5), (81, 6), (16, 16)], [(32, 3), (16, 1), (96, 70)]])
+@pytest.mark.parametrize("lims", [9, 11, 13])
+def test_float32_rows_that_start_on_64_bytes_and_elsewhere(sides, lims, gpu):
+    """The float32 state is stored past the caches where every row of the
+    planar layout starts on 64 bytes and through them elsewhere: each instance
+    of an ensemble, in both kernels, against its own run."""
+    from paper_2411_15001_amd.solver import BatchSolver
+
+    u0s = [field(nx, ny, 40 + i) for i, (nx, ny) in enumerate(sides)]
+    kw = dict(limiters=lims, a_beta=1.1, bc_x=1, bc_y=0, precision=1)
+    single = [run(u, kw, None, steps=6) for u in u0s]
+    for launch in (None, (4, 3)):
+        b = BatchSolver(u0s, **kw)
+        if launch:
+            b.set_launch(*launch)
+        b.step(6)
+        for i, one in enumerate(single):
+            assert gpu.equal(b.moments(i), one[0][:4].double())
+        b.close()
