@@ -354,7 +354,7 @@ vlbm::StepArgs make_args(const lbm_ctx* c, const void* src, void* dst, int slot)
   a.xcd_remap = c->xcd;
   a.groups = compute_groups(c);
   a.rows = c->rows;
-  a.ragged = c->ragged;
+  a.past = vlbm::store_past(c->p.precision, c->plane, !c->ragged, c->rows) ? 1 : 0;
   a.sc = c->sc;
   if (c->n_inst > 1)
     a.bnd_table = (const vlbm::BndDesc*)(c->ws + c->lay.bndt);

@@ -122,7 +122,7 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   a.waves_per_group = 4;
   a.xcd_remap = 1;
   a.rows = rows;
-  a.ragged = vlbm::even_rows(in, cells) ? 0 : 1;
+  a.past = vlbm::store_past(p->precision, cells, vlbm::even_rows(in, cells), rows) ? 1 : 0;
   a.groups = (int)(((rows ? a.n_items : (a.n_items + 3) / 4) + 7) / 8 * 8);
   a.sc = sc;
   a.bnd = 0;

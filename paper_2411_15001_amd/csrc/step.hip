@@ -227,19 +227,11 @@ __device__ __forceinline__ double face_theta(const Scheme& s, const C us[4], con
   return t;
 }
 
-// Store of the new state.  With the float32 state the stores bypass cache
-// allocation (non-temporal): the state is written once and read by the next
-// launch from HBM anyway, and this measured 2% faster on the 8192^2 blast;
-// with float64 it measured 3% slower, so plain stores are kept there.  Past
-// the caches a wave's 256 bytes cost a read-modify-write at each end that does
-// not meet a line, so rows that start anywhere (NT = false, StepArgs::ragged)
-// are stored through L2, where the neighbouring strip completes the line.  us a
-// step, float32 state, non-temporal / through L2: 2001 x 2047 PP 208 / 171, LMP
-// 247 / 190; 4001^2 805 / 617, 934 / 727; 1000 x 1001 PP 50 / 40; 801 x 799
-// 35 / 27; with rows on 64 bytes 4000^2 PP 538 / 554, 2000 x 2048 164 / 167.
-template <bool NT = true, class T>
+// Store of the new state: NT past the caches (non-temporal), else through L2
+// (see store_past for which and why).
+template <bool NT, class T>
 __device__ __forceinline__ void put(T* p, T v) {
-  if constexpr (NT && sizeof(T) == 4)
+  if constexpr (NT)
     __builtin_nontemporal_store(v, p);
   else
     *p = v;
@@ -759,14 +751,14 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
       } else {
         if (row0 && lane_out) {
           const unsigned o = (unsigned)L * unx + (unsigned)gi;
-          put(&(dbase + (4 + c) * P)[o], (T)u1n);
-          put(&(dbase + (8 + c) * P)[o], (T)u2n);
-          put(&(dbase + (12 + c) * P)[o], (T)u3n);
+          put<NT>(&(dbase + (4 + c) * P)[o], (T)u1n);
+          put<NT>(&(dbase + (8 + c) * P)[o], (T)u2n);
+          put<NT>(&(dbase + (12 + c) * P)[o], (T)u3n);
         }
         if (row1 && lane_out) {
           const unsigned o = (unsigned)(L - 1) * unx + (unsigned)gi;
-          put(&(dbase + c * P)[o], (T)fin[c]);
-          put(&(dbase + (16 + c) * P)[o], (T)u4n);
+          put<NT>(&(dbase + c * P)[o], (T)fin[c]);
+          put<NT>(&(dbase + (16 + c) * P)[o], (T)u4n);
         }
       }
       pP[c] = s;
@@ -866,16 +858,16 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int
     if (sw1) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        put(&(dbase + (4 + c) * P)[so1], sv[c]);
-        put(&(dbase + (8 + c) * P)[so1], sv[4 + c]);
-        put(&(dbase + (12 + c) * P)[so1], sv[8 + c]);
+        put<NT>(&(dbase + (4 + c) * P)[so1], sv[c]);
+        put<NT>(&(dbase + (8 + c) * P)[so1], sv[4 + c]);
+        put<NT>(&(dbase + (12 + c) * P)[so1], sv[8 + c]);
       }
     }
     if (sw2) {
 #pragma unroll
       for (int c = 0; c < 4; ++c) {
-        put(&(dbase + c * P)[so2], sv[12 + c]);
-        put(&(dbase + (16 + c) * P)[so2], sv[16 + c]);
+        put<NT>(&(dbase + c * P)[so2], sv[12 + c]);
+        put<NT>(&(dbase + (16 + c) * P)[so2], sv[16 + c]);
       }
     }
   };
@@ -1198,7 +1190,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // multiple of 64 (every strip full) and that have no boundary descriptions.
 // The loads into LDS are not tracked by the compiler's wait counters:
 // the march waits on the vector-memory counter itself (see the loop head).
-template <class T, class C, int LIMS, bool TH, bool BLK>
+template <class T, class C, int LIMS, bool TH, bool BLK, bool NT>
 __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                               int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
@@ -1462,13 +1454,13 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
       const C u4n = pM4 + tB * pd4;
       fin[c] = qP[c] + (u4n - tB * qd3[c]);
       if (row1) {
-        put(out_at(4 + c, L - 1), (T)u1n);
-        put(out_at(8 + c, L - 1), (T)u2n);
-        put(out_at(12 + c, L - 1), (T)u3n);
+        put<NT>(out_at(4 + c, L - 1), (T)u1n);
+        put<NT>(out_at(8 + c, L - 1), (T)u2n);
+        put<NT>(out_at(12 + c, L - 1), (T)u3n);
       }
       if (row2) {
-        put(out_at(c, L - 2), (T)fin[c]);
-        put(out_at(16 + c, L - 2), (T)u4n);
+        put<NT>(out_at(c, L - 2), (T)fin[c]);
+        put<NT>(out_at(16 + c, L - 2), (T)u4n);
       }
       qP[c] = s;
       qM3[c] = pM3;
@@ -1532,7 +1524,7 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
 // blocked state of a context (single instance, width a multiple of 64, no
 // boundary descriptions), where a strip row is one contiguous range; planar
 // states take march_short.
-template <class T, class C, int LIMS, bool TH, bool BLK>
+template <class T, class C, int LIMS, bool TH, bool BLK, bool NT>
 __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                                 int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
@@ -1718,13 +1710,13 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
       const C u4n = M[3][c] + tB * d[3][c];
       fin[c] = pP[c] + (u4n - tB * pd3[c]);
       if (row0) {
-        put(out_at(4 + c, L), (T)u1n);
-        put(out_at(8 + c, L), (T)u2n);
-        put(out_at(12 + c, L), (T)u3n);
+        put<NT>(out_at(4 + c, L), (T)u1n);
+        put<NT>(out_at(8 + c, L), (T)u2n);
+        put<NT>(out_at(12 + c, L), (T)u3n);
       }
       if (row1) {
-        put(out_at(c, L - 1), (T)fin[c]);
-        put(out_at(16 + c, L - 1), (T)u4n);
+        put<NT>(out_at(c, L - 1), (T)fin[c]);
+        put<NT>(out_at(16 + c, L - 1), (T)u4n);
       }
       pP[c] = s;
     }
@@ -2017,7 +2009,7 @@ __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in,
   auto store = [&](int q, C v) {
     if (!lane_out) return;
     if constexpr (BLK)
-      put(dbase + ((long long)j * nx + x0) * 20 + q * 64 + lane, (T)v);
+      put<NT>(dbase + ((long long)j * nx + x0) * 20 + q * 64 + lane, (T)v);
     else
       put<NT>(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
   };
@@ -2162,7 +2154,7 @@ __device__ __forceinline__ RowEvents step_row(const StepArgs& A, const Inst& in,
 // when its turn comes.  step_row's 192 leave two: 384^2 18.7 us a step against
 // 15.9 here, 768^2 50.0 / 45.3, 896^2 66.7 / 62.3; where no SIMD has more than
 // one wave, up to 256 workgroups, its loads at once are better (64^2 8.0 / 8.4).
-template <int LIMS, bool TH, bool BLK>
+template <int LIMS, bool TH, bool BLK, bool NT>
 __device__ __forceinline__ RowEvents step_row_late(const StepArgs& A, const Inst& in, int ii, int xs, int j, int lane,
                                                    const Slots* shard) {
   using T = double;
@@ -2276,9 +2268,9 @@ __device__ __forceinline__ RowEvents step_row_late(const StepArgs& A, const Inst
   auto store = [&](int q, C v) {
     if (!lane_out) return;
     if constexpr (BLK)
-      put(&(dbase + ((long long)j * nx + x0) * 20 + q * 64)[(unsigned)lane], (T)v);
+      put<NT>(&(dbase + ((long long)j * nx + x0) * 20 + q * 64)[(unsigned)lane], (T)v);
     else
-      put(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
+      put<NT>(&(dbase + q * P)[(unsigned)j * (unsigned)nx + (unsigned)gi], (T)v);
   };
   unsigned n_guard = 0, n_lim = 0;
   C mu = C(0), nu = C(0), rs0 = C(0), rn0 = C(0);  // bounds of the cell, density of its y-faces
@@ -2473,9 +2465,8 @@ __device__ __forceinline__ RowEvents step_row_late(const StepArgs& A, const Inst
 // whether the face factors are written (with LIMS = 0 they are written
 // whenever A.theta_x is set), BND whether boundary descriptions are read
 // (only with LIMS = 0), DMA the LDS-staged marches, BLK the blocked state
-// layout (with DMA only), NT how the float32 state is stored (see put).
-template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool DMA = false, bool BLK = false,
-          bool NT = true>
+// layout (with DMA only), NT stores past the caches.
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool DMA, bool BLK, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE, WPE)))
 void step_kernel(StepArgs A) {
   const int lane = threadIdx.x & 63;
@@ -2503,11 +2494,11 @@ void step_kernel(StepArgs A) {
     const int xs = (int)(local % in.xs);
     const int ys = (int)(local / in.xs);
     if constexpr (LMP && DMA)
-      march_lmp_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
+      march_lmp_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, item, xs, ys, lane, wave);
     else if constexpr (LMP)
       march_lmp<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
     else if constexpr (DMA)
-      march_short_dma<T, C, LIMS, TH, BLK>(A, in, ii, item, xs, ys, lane, wave);
+      march_short_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, item, xs, ys, lane, wave);
     else
       march_short<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
   }
@@ -2550,7 +2541,7 @@ __device__ __forceinline__ void edges_first(int X, int Y, int groups, int block,
 
 // The row kernel: a workgroup of four waves takes four rows of a strip, one
 // row per wave (the strip table is built for strips of four rows).
-template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK, bool LATE = false, bool NT = true>
+template <class T, class C, bool LMP, int WPE, int LIMS, bool TH, bool BND, bool BLK, bool LATE, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE)))
 void row_kernel(StepArgs A) {
   const int lane = threadIdx.x & 63;
@@ -2581,7 +2572,7 @@ void row_kernel(StepArgs A) {
   RowEvents ev = {0.0, {}};
   if (j < in.ny) {
     if constexpr (LATE)
-      ev = step_row_late<LIMS, TH, BLK>(A, in, ii, xs, j, lane, shard);
+      ev = step_row_late<LIMS, TH, BLK, NT>(A, in, ii, xs, j, lane, shard);
     else
       ev = step_row<T, C, LMP, LIMS, TH, BND, BLK, NT>(A, in, ii, xs, j, lane, shard);
   }
@@ -2698,11 +2689,11 @@ __global__ __launch_bounds__(256) void percell_kernel(StepArgs A) {
       un = un + (u3n - tC * d4);
       un = un + (u4n - tC * d3);
       fin[k] = un;
-      put(&D[k * P + oc], un);
-      put(&D[(4 + k) * P + oc], u1n);
-      put(&D[(8 + k) * P + oc], u2n);
-      put(&D[(12 + k) * P + oc], u3n);
-      put(&D[(16 + k) * P + oc], u4n);
+      put<sizeof(T) == 4>(&D[k * P + oc], un);
+      put<sizeof(T) == 4>(&D[(4 + k) * P + oc], u1n);
+      put<sizeof(T) == 4>(&D[(8 + k) * P + oc], u2n);
+      put<sizeof(T) == 4>(&D[(12 + k) * P + oc], u3n);
+      put<sizeof(T) == 4>(&D[(16 + k) * P + oc], u4n);
     }
     n_lim += (thC < 1.0);
     // face states of the cell's four faces (eq. (12)): the guard of the west
@@ -3136,9 +3127,9 @@ __global__ __launch_bounds__(256) void bnd_lambda_kernel(StepArgs A, int slot) {
 // for every limiter set with density bounds (fixed at compile time for the
 // LMP and RLMP sets with PP and pressure).  Its LDS (three rows per wave) is
 // dynamic, above the default limit in float64.
-template <class T, bool LMP, int WPE, int LIMS, bool TH, bool BLK>
+template <class T, bool LMP, int WPE, int LIMS, bool TH, bool BLK, bool NT>
 static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) {
-  const auto k = step_kernel<T, T, LMP, WPE, LIMS, TH, false, true, BLK>;
+  const auto k = step_kernel<T, T, LMP, WPE, LIMS, TH, false, true, BLK, NT>;
   // the limit is a property of the function on each device: raise it on the
   // first launch on every device (a failure leaves the error for the
   // launcher's hipGetLastError, and the launch itself then fails too)
@@ -3160,7 +3151,7 @@ static void launch_dma(const StepArgs& a, dim3 grid, dim3 block, hipStream_t s) 
 // boundary descriptions too, the rest with the set read at run time.  (Read at
 // run time, boundary descriptions: 1500 x 500 float64 RLMP 80 us a step, fixed
 // 76; 2000^2 451 / 438; PP 1500 x 500 49.5 / 47; float32 PP 1000^2 56.6 / 55.)
-template <class T, bool LMP, int WPE, bool BLK, bool LATE = false, bool NT = true>
+template <class T, bool LMP, int WPE, bool BLK, bool LATE, bool NT>
 static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
   constexpr int kRelaxed = 1 | 4 | 8;
@@ -3189,7 +3180,7 @@ static void launch_rows(const StepArgs& a, int lims, dim3 grid, hipStream_t s) {
 
 static bool dma_ok(const StepArgs& a) { return a.n_inst == 1 && a.inst0.nx % 64 == 0 && !a.bnd; }
 
-template <class T, bool LMP, int WPE, bool NT = true>
+template <class T, bool LMP, int WPE, bool NT>
 static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, hipStream_t s) {
   constexpr int kFixed = LMP ? (1 | 2 | 8) : (1 | 8);
   constexpr int kRelaxed = 1 | 4 | 8;  // (bounds-limited sets only)
@@ -3197,18 +3188,18 @@ static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, h
     // a context's blocked state: the LDS-staged marches (every instance's
     // width is a multiple of 64 and no instance has boundary descriptions)
     if (lims == kFixed && a.theta_x)
-      launch_dma<T, LMP, WPE, kFixed, true, true>(a, grid, block, s);
+      launch_dma<T, LMP, WPE, kFixed, true, true, NT>(a, grid, block, s);
     else if (lims == kFixed)
-      launch_dma<T, LMP, WPE, kFixed, false, true>(a, grid, block, s);
+      launch_dma<T, LMP, WPE, kFixed, false, true, NT>(a, grid, block, s);
     else if constexpr (LMP) {
       if (lims == kRelaxed && a.theta_x)
-        launch_dma<T, LMP, WPE, kRelaxed, true, true>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kRelaxed, true, true, NT>(a, grid, block, s);
       else if (lims == kRelaxed)
-        launch_dma<T, LMP, WPE, kRelaxed, false, true>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kRelaxed, false, true, NT>(a, grid, block, s);
       else
-        launch_dma<T, LMP, WPE, 0, false, true>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, 0, false, true, NT>(a, grid, block, s);
     } else {
-      launch_dma<T, LMP, WPE, 0, false, true>(a, grid, block, s);
+      launch_dma<T, LMP, WPE, 0, false, true, NT>(a, grid, block, s);
     }
     return;
   }
@@ -3217,15 +3208,15 @@ static void launch_step_as(const StepArgs& a, int lims, dim3 grid, dim3 block, h
       // PP + LMP + pressure and PP + RLMP + pressure with the set fixed;
       // every other set, and sponge layers, with the set read at run time
       if (lims == kFixed && a.theta_x)
-        launch_dma<T, LMP, WPE, kFixed, true, false>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kFixed, true, false, NT>(a, grid, block, s);
       else if (lims == kFixed)
-        launch_dma<T, LMP, WPE, kFixed, false, false>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kFixed, false, false, NT>(a, grid, block, s);
       else if (lims == kRelaxed && a.theta_x)
-        launch_dma<T, LMP, WPE, kRelaxed, true, false>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kRelaxed, true, false, NT>(a, grid, block, s);
       else if (lims == kRelaxed)
-        launch_dma<T, LMP, WPE, kRelaxed, false, false>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, kRelaxed, false, false, NT>(a, grid, block, s);
       else
-        launch_dma<T, LMP, WPE, 0, false, false>(a, grid, block, s);
+        launch_dma<T, LMP, WPE, 0, false, false, NT>(a, grid, block, s);
       return;
     }
   }
@@ -3257,45 +3248,42 @@ hipError_t launch_bnd_lambda(const StepArgs& a, int slot, hipStream_t s) {
   return hipGetLastError();
 }
 
+template <bool NT>
+static void launch_rows_as(const StepArgs& a, int precision, bool lmp, int lims, dim3 grid, hipStream_t s) {
+  if (precision == 0 && lmp && a.n_items > 256 && !a.bnd)
+    a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, true, true, NT>(a, lims, grid, s)
+              : launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, false, true, NT>(a, lims, grid, s);
+  else if (precision == 0 && lmp)
+    a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, true, false, NT>(a, lims, grid, s)
+              : launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, false, false, NT>(a, lims, grid, s);
+  else if (precision == 0)
+    a.blocked ? launch_rows<double, false, VLBM_WPE_ROW_F64, true, false, NT>(a, lims, grid, s)
+              : launch_rows<double, false, VLBM_WPE_ROW_F64, false, false, NT>(a, lims, grid, s);
+  else if (lmp)
+    a.blocked ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, true, false, NT>(a, lims, grid, s)
+              : launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false, false, NT>(a, lims, grid, s);
+  else
+    a.blocked ? launch_rows<float, false, VLBM_WPE_ROW_F32, true, false, NT>(a, lims, grid, s)
+              : launch_rows<float, false, VLBM_WPE_ROW_F32, false, false, NT>(a, lims, grid, s);
+}
+
 hipError_t launch_step(const StepArgs& a, int precision, hipStream_t s) {
   if (a.blocked && (a.bnd || (a.n_inst == 1 && a.inst0.nx % 64 != 0))) return hipErrorInvalidValue;
   const bool lmp = (a.sc.limiters & 6u) != 0 && a.sc.order == 2;
   const int lims = (a.sc.order == 2 && a.sc.sponge == 0 && a.sc.eps <= 1e-12) ? a.sc.limiters : 0;
   const dim3 block(64 * a.waves_per_group);
   const dim3 grid(a.groups);
-  if (a.rows) {
-    if (precision == 0 && lmp && a.n_items > 256 && !a.bnd)
-      a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, true, true>(a, lims, grid, s)
-                : launch_rows<double, true, VLBM_WPE_ROW_F64_LATE, false, true>(a, lims, grid, s);
-    else if (precision == 0 && lmp)
-      a.blocked ? launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, true>(a, lims, grid, s)
-                : launch_rows<double, true, VLBM_WPE_ROW_F64_LMP, false>(a, lims, grid, s);
-    else if (precision == 0)
-      a.blocked ? launch_rows<double, false, VLBM_WPE_ROW_F64, true>(a, lims, grid, s)
-                : launch_rows<double, false, VLBM_WPE_ROW_F64, false>(a, lims, grid, s);
-    else if (lmp)
-      a.blocked ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, true>(a, lims, grid, s)
-      : a.ragged  ? launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false, false, false>(a, lims, grid, s)
-                : launch_rows<float, true, VLBM_WPE_ROW_F32_LMP, false>(a, lims, grid, s);
-    else
-      a.blocked ? launch_rows<float, false, VLBM_WPE_ROW_F32, true>(a, lims, grid, s)
-      : a.ragged  ? launch_rows<float, false, VLBM_WPE_ROW_F32, false, false, false>(a, lims, grid, s)
-                : launch_rows<float, false, VLBM_WPE_ROW_F32, false>(a, lims, grid, s);
-    return hipGetLastError();
-  }
-  if (precision == 0) {
-    if (lmp)
-      launch_step_as<double, true, VLBM_WPE_F64_LMP>(a, lims, grid, block, s);
-    else
-      launch_step_as<double, false, VLBM_WPE_F64>(a, lims, grid, block, s);
-  } else {
-    if (lmp)
-      a.ragged ? launch_step_as<float, true, VLBM_WPE_F32_LMP, false>(a, lims, grid, block, s)
-               : launch_step_as<float, true, VLBM_WPE_F32_LMP>(a, lims, grid, block, s);
-    else
-      a.ragged ? launch_step_as<float, false, VLBM_WPE_F32, false>(a, lims, grid, block, s)
-               : launch_step_as<float, false, VLBM_WPE_F32>(a, lims, grid, block, s);
-  }
+  if (a.rows)
+    a.past ? launch_rows_as<true>(a, precision, lmp, lims, grid, s) : launch_rows_as<false>(a, precision, lmp, lims, grid, s);
+  else if (precision == 0)
+    lmp ? launch_step_as<double, true, VLBM_WPE_F64_LMP, false>(a, lims, grid, block, s)
+        : launch_step_as<double, false, VLBM_WPE_F64, false>(a, lims, grid, block, s);
+  else if (lmp)
+    a.past ? launch_step_as<float, true, VLBM_WPE_F32_LMP, true>(a, lims, grid, block, s)
+           : launch_step_as<float, true, VLBM_WPE_F32_LMP, false>(a, lims, grid, block, s);
+  else
+    a.past ? launch_step_as<float, false, VLBM_WPE_F32, true>(a, lims, grid, block, s)
+           : launch_step_as<float, false, VLBM_WPE_F32, false>(a, lims, grid, block, s);
   return hipGetLastError();
 }
 

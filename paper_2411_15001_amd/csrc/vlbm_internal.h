@@ -104,16 +104,39 @@ struct StepArgs {
   int blocked;            // src and dst hold the blocked layout (a context's own
                           // buffers; every width a multiple of 64, no boundary
                           // descriptions), else planar
-  int ragged;             // some row of the planar layout does not start on a
-                          // multiple of 16 elements (64 bytes of float32)
+  int past;               // 1: the new state is stored past the caches (store_past)
   int rows;               // 1: the row kernel (one row of a strip per wave; the
                           // strips are kRowsPerGroup rows high and groups counts
                           // them), 0: the marches
   Scheme sc;
 };
 
+// Whether a step stores the new state past the caches (non-temporal) rather than
+// through L2.  cells: of all instances; even: see even_rows; rows: the row
+// kernel.  us a step, past / through:
+// - A small state (17 MB, half of what the XCDs' L2s hold) is better not left
+//   dirty in an L2 whose lines the launch's end writes back: float32 384^2 PP
+//   8.8 / 9.7, 448^2 10.1 / 11.4, 401^2 LMP 11.8 / 12.6; float64 256^2 PP 7.65 /
+//   8.2, 320^2 10.2 / 11.2, but 352^2 14.8 / 13.6.
+// - Beyond that, while the old and the new state fit the last-level cache, the
+//   next step finds there what went through: float32 640^2 PP 20.4 / 18.7,
+//   896^2 33.6 / 29.0, 1280^2 67.4 / 59.2, LMP 79.9 / 75; float64 512^2 PP 25.3 /
+//   19.4, LMP 31 / 23.8.
+// - Larger float32 states are read from memory anyway: 4096^2 PP 509 / 525,
+//   8192^2 2% in favour of past; float64 there 3% in favour of through.
+// - A row that starts off 64 bytes leaves a partial line at both ends of each
+//   strip, which past the caches costs a read-modify-write and through L2 is
+//   completed by the neighbouring strip: float32 2001 x 2047 PP 208 / 172, LMP
+//   247 / 191; 4001^2 801 / 618, 933 / 730; 801 x 799 35 / 27; float64 257^2
+//   10.9 / 10.1 (small float32 states are better past all the same).
+inline bool store_past(int precision, long long cells, bool even, bool rows) {
+  const bool small = cells * (precision == 0 ? 160 : 80) <= 17000000;
+  if (precision == 0) return rows && small && even;
+  return small || (even && cells * 160 > (256ll << 20));
+}
+
 // Whether an instance's rows in the planar layout start on multiples of 16
-// elements only.
+// elements only (64 bytes with the float32 state).
 inline bool even_rows(const Inst& in, long long plane) { return ((in.nx | in.off | plane) & 15) == 0; }
 
 // Rows of a strip that one workgroup of the row kernel takes, one per wave.

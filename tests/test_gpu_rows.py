@@ -179,12 +179,23 @@ def test_autotuned_choice_keeps_the_results(gpu, tmp_path):
         s.close()
 
 
+@pytest.mark.parametrize("nx,ny,prec", [(320, 320, 0), (336, 320, 0), (321, 320, 0), (448, 448, 1), (464, 464, 1),
+                                        (447, 448, 1), (1280, 1280, 1), (1344, 1280, 1), (1281, 1320, 1)])
+@pytest.mark.parametrize("lims", [9, 11])
+def test_both_sides_of_the_store_rule(nx, ny, prec, lims, gpu):
+    """The state is stored past the caches or through L2 by its size and by how
+    its rows are aligned: around the limits, in both kernels."""
+    print("store", nx, ny, prec, lims, flush=True)
+    kw = dict(limiters=lims, a_beta=1.1, bc_x=1, bc_y=1, precision=prec)
+    u0 = np.ascontiguousarray(cases.double_rarefaction(max(nx, ny))[:, :ny, :nx])
+    check(run(u0, kw, None, steps=3), run(u0, kw, (20, 3), steps=3), gpu)
+
+
 @pytest.mark.parametrize("sides", [[(48, 5), (80, 6)], [(48, 5), (81, 6), (16, 16)], [(32, 3), (16, 1), (96, 70)]])
 @pytest.mark.parametrize("lims", [9, 11, 13])
 def test_float32_rows_that_start_on_64_bytes_and_elsewhere(sides, lims, gpu):
-    """The float32 state is stored past the caches where every row of the
-    planar layout starts on 64 bytes and through them elsewhere: each instance
-    of an ensemble, in both kernels, against its own run."""
+    """Instances whose rows start on 64 bytes and others, in one buffer: each, in
+    both kernels, against its own run."""
     from paper_2411_15001_amd.solver import BatchSolver
 
     u0s = [field(nx, ny, 40 + i) for i, (nx, ny) in enumerate(sides)]
