@@ -8,7 +8,9 @@
 // the two edge lanes also load the halo column beside the strip and evaluate
 // the faces and bounds that reach across it.  y-neighbours are the rows the
 // lane already holds in registers from the previous iterations.  No barrier
-// is used; LDS only receives the rows of the LDS-staged marches.
+// is used; LDS only receives the rows of the LDS-staged marches.  Small grids
+// and described boundaries take the row kernel instead: one row of a strip per
+// wave, its neighbours' rows loaded with it (use_rows for the sizes).
 //
 // State layouts.  Planar: value q of cell c (row-major over the instance) at
 // q * plane + c.  Blocked (a context's own buffers when every instance's
@@ -38,8 +40,8 @@
 //
 // The wavespeed of every new cell (Section 4 preamble) is reduced over the
 // wave with lane shuffles and merged with one 64-bit atomic max per strip
-// into the instance's next lambda slot; the next launch derives a^{n+1} from
-// it on the device.
+// into the instance's next lambda slot or one of its further records (kShards);
+// the next launch derives a^{n+1} from the largest on the device.
 
 #include <math.h>
 
@@ -3120,7 +3122,7 @@ __global__ __launch_bounds__(256) void bnd_lambda_kernel(StepArgs A, int slot) {
 // with the set, and whether the face factors are written, fixed at compile
 // time (same results; A/B on one box: 2% faster in float64 and on the
 // ensembles, 4% on the LMP runs); all other configurations run the general
-// kernels, and a grid with boundary descriptions the general kernels that
+// kernels, and marches with boundary descriptions the general kernels that
 // read them.
 // The LDS-staged bounds-limited march needs every strip full (width a
 // multiple of 64), a single instance and no boundary descriptions; it runs

@@ -147,21 +147,22 @@ constexpr int kRowsPerGroup = 4;
 // 1024 strips of several rows to fill the chip and spends two (four under
 // density bounds) further rows on each; the row kernel has a wave for every
 // row, evaluates the faces between rows twice and reads its neighbours' rows
-// through the caches.  Measured on the blast and the near-vacuum rarefaction,
-// us per step, row kernel against the best march: 64^2 float64 PP 7.3 / 19.7,
-// 512^2 20.2 / 24.8, 896^2 49.8 / 54.2, 960^2 74.4 / 67.7 (the two states no
-// longer fit the last-level cache); under LMP 512^2 25.3 / 32.0, 896^2 66.9 /
-// 66.1, 960^2 89.9 / 75.9; float32 state, LMP: 832^2 42.2 / 46.2, 896^2 50.5 /
-// 47.5.  Ensembles, whose march strips end ragged at every instance: 24 of
-// 128..512 (33920 strip rows) 158 / 164, 32 of them (44544) 195 / 198; under LMP
-// 64 of 40..200 (19502) 113 / 132, 10 of 200..600 (26904) 151 / 149.  With
-// boundary descriptions every row of a march checks for ghosts, here only
-// the rows and strips at the edges: float64 LMP 400^2 32.8 / 63.1, 3000^2 964 / 1145.
+// through the caches, which it needs to hold both states.  us a step, row kernel /
+// best march (strips of 4 to 16 rows), near-vacuum rarefaction: float64 PP 64^2
+// 7.3 / 19.7, 512^2 19.8 / 23.5, 901^2 47.7 / 51.7 (13515 strip rows), 960^2 69.6 /
+// 65.7; LMP 512^2 24.6 / 31.9, 901^2 68.4 / 71.1, 960^2 91 / 78; float32 PP 832^2
+// 25.8 / 32.0, 1024^2 34.1 / 36.0; LMP 896^2 43.8 / 47.6, 960^2 49.2 / 48.3, 1024^2
+// 58 / 49.  Ensembles, whose march strips end ragged at every instance: float64
+// PP 24 of 128..512 (33920 strip rows) 161 / 173, 20 of 200..600 (56415) 260 / 283;
+// LMP 64 of 40..200 (19502) 113 / 138, 24 of 128..512 187 / 183; float32 PP 88 /
+// 89.4 with 33920 and 112 / 106 with 44544, LMP 105 / 107 and 137 / 126.  With boundary descriptions every row
+// of a march checks for ghosts, here only the rows and strips at the edges:
+// float64 LMP 400^2 32.2 / 63.1, 3000^2 964 / 1145.
 inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, const Scheme& sc) {
   if (bnd) return true;
   const bool lmp = (sc.limiters & 6) != 0 && sc.order == 2;
-  if (n_inst > 1) return strip_rows <= (lmp ? 24000 : 40000);
-  return strip_rows <= (lmp && precision != 0 ? 11000 : 12600);
+  if (n_inst > 1) return strip_rows <= (precision != 0 ? 36000 : lmp ? 24000 : 57000);
+  return strip_rows <= (precision == 0 ? 13600 : lmp ? 12600 : 16400);
 }
 
 // Rows per strip of a march whose launch shape nobody set: the height with the

@@ -149,6 +149,21 @@ def test_both_sides_of_the_size_rule(nx, ny, rows, gpu):
     check(a, b, gpu)
 
 
+@pytest.mark.parametrize("nx,ny,lims,prec,rows", [(900, 900, 11, 0, True), (960, 920, 11, 0, False),
+                                                  (1024, 1025, 9, 1, True), (1024, 1026, 9, 1, False),
+                                                  (896, 900, 13, 1, True), (896, 901, 13, 1, False)])
+def test_size_rule_by_type_and_bounds(nx, ny, lims, prec, rows, gpu):
+    from paper_2411_15001_amd.solver import Solver
+
+    kw = dict(limiters=lims, precision=prec, bc_x=1, bc_y=1)
+    u0 = np.ascontiguousarray(cases.double_rarefaction(max(nx, ny))[:, :ny, :nx])
+    s = Solver(u0, **kw)
+    groups = -(-((nx + 63) // 64 * ((ny + 3) // 4)) // 8) * 8  # a multiple of the XCDs
+    assert (B.lbm_get_grid(s.ctx)[1] == groups) == rows
+    s.close()
+    check(run(u0, kw, None, steps=3), run(u0, kw, (20, 3), steps=3), gpu)
+
+
 @pytest.mark.parametrize("nx,ny", [(1100, 1030), (1024, 2048)])
 @pytest.mark.parametrize("lims,prec", [(9, 0), (11, 0), (9, 1), (13, 1)])
 def test_chosen_strip_height_keeps_the_results(nx, ny, lims, prec, gpu):
