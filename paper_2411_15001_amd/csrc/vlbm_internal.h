@@ -123,7 +123,9 @@ struct StepArgs {
 //   896^2 33.6 / 29.0, 1280^2 67.4 / 59.2, LMP 79.9 / 75; float64 512^2 PP 25.3 /
 //   19.4, LMP 31 / 23.8.
 // - Larger float32 states are read from memory anyway: 4096^2 PP 509 / 525,
-//   8192^2 2% in favour of past; float64 there 3% in favour of through.
+//   8192^2 2% in favour of past.  Float64 there is within 1.5% either way with even
+//   rows (8192^2 PP 3936 / 3925, LMP 3979 / 4036, 2048^2 277 / 275) and loses with
+//   others (2001^2 353 / 299), so it goes through.
 // - A row that starts off 64 bytes leaves a partial line at both ends of each
 //   strip, which past the caches costs a read-modify-write and through L2 is
 //   completed by the neighbouring strip: float32 2001 x 2047 PP 208 / 172, LMP
