@@ -149,8 +149,9 @@ struct lbm_ctx {
   Slots* slots = nullptr;
   Slots* shards = nullptr;  // [n_inst][n_shards], or the slots (one shard: small grids, per-cell blending)
   int n_shards = 1;
-  // whether steps ran since the shards were last folded; a step that the
-  // caller records into a graph may be replayed at any time after (recorded)
+  // whether steps ran since the shards were last folded; work that raises
+  // counters and that the caller records into a graph may be replayed at any
+  // time after (recorded)
   bool raised = false, recorded = false;
   // every counter is zero: lbm_moments cleared them and nothing that counts
   // was enqueued since
@@ -410,12 +411,18 @@ bool being_recorded(lbm_ctx* c) {
   return true;
 }
 
+// Called where work that may raise a counter is enqueued: the next read has to
+// look at the counters, and every read once such work was recorded.
+void note_counts(lbm_ctx* c) {
+  c->clean = false;
+  if (!c->recorded) c->recorded = being_recorded(c);
+}
+
 // Called where steps are enqueued: the shards need a fold before the next
 // read, and before every read once steps were recorded.
 void note_steps(lbm_ctx* c) {
   c->raised = true;
-  c->clean = false;
-  if (!c->recorded) c->recorded = being_recorded(c);
+  note_counts(c);
 }
 
 // Folds the shards into the slot records, where steps may have raised them;
@@ -858,7 +865,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
                                              c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "set_state copy");
   const int slot = (int)(c->step % 3);
-  c->clean = false;  // (non-admissible cells of the state are counted)
+  note_counts(c);  // (non-admissible cells of the state are counted)
   if (e == hipSuccess) e = fold_shards(c, slot);
   if (e == hipSuccess)
     e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(),
@@ -1275,7 +1282,7 @@ extern "C" lbm_status lbm_step_adjoint_theta(lbm_ctx* c, const double* U, const 
   // a^n: fixed, or from lambda^n of U_n in the slot the next forward step
   // clears before it reads it (no other slot is touched)
   const int scratch = (int)((c->step + 2) % 3);
-  c->clean = false;  // (the reduction below counts non-admissible cells of U_n)
+  note_counts(c);  // (the reduction below counts non-admissible cells of U_n)
   hipError_t e = hipSuccess;
   if (c->p.a_mode != LBM_A_FIXED) {
     e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
@@ -1303,7 +1310,7 @@ extern "C" lbm_status lbm_step_adjoint(lbm_ctx* c, const double* U, const double
   // lambda^n of U (scratch slot: a second Slots record is not available, so
   // use the slot that the next forward step would clear)
   const int scratch = (int)((c->step + 2) % 3);
-  c->clean = false;
+  note_counts(c);
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)&c->slots[0].lam[scratch], 0u, 2, c->stream);
   if (e == hipSuccess)
     e = vlbm::launch_lambda_state(c->sc, c->insts.data(), nullptr, 1, c->plane, U, c->slots, scratch,

@@ -1,0 +1,85 @@
+"""The events that lbm_moments reports: whatever raised them (eager work, or
+loads and adjoint steps that the caller recorded into a graph and replays), the
+next call returns them and the one after it starts from zero."""
+import pytest
+
+from paper_2411_15001_amd import binding as B
+from paper_2411_15001_amd import cases
+
+pytestmark = pytest.mark.gpu
+
+KW = dict(limiters=1 | 2 | 8, a_beta=1.1, bc_x=1, bc_y=1)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def gpu():
+    import torch
+
+    assert torch.cuda.is_available()
+    B.lib()
+    return torch
+
+
+def record(kind, s, state, torch):
+    """A graph of one call that counts the non-admissible cells of `state`."""
+    bar, out = torch.ones_like(state), torch.empty_like(state)
+    tx = torch.ones((s.ny, s.nx + 1), dtype=torch.float64, device="cuda")
+    ty = torch.ones((s.ny + 1, s.nx), dtype=torch.float64, device="cuda")
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+        if kind == "load":
+            s.set_state(state)
+        elif kind == "adjoint":
+            B.lbm_step_adjoint(s.ctx, state, bar, out)
+        else:
+            B.lbm_step_adjoint_theta(s.ctx, state, tx, ty, bar, out)
+    return g, (bar, out, tx, ty)
+
+
+@pytest.mark.parametrize("kind", ["load", "adjoint", "adjoint_theta"])
+@pytest.mark.parametrize("n", [64, 100])  # blocked and planar layouts
+def test_replays_of_recorded_work_that_counts_are_reported(kind, n, gpu):
+    from paper_2411_15001_amd.solver import Solver
+
+    print("events", kind, n, flush=True)
+    torch = gpu
+    with torch.cuda.stream(torch.cuda.Stream()):
+        s = Solver(cases.riemann4(n, seed=5), **KW)
+        s.step(6)
+        good = s.get_state()
+        state = good.clone()
+        g, keep = record(kind, s, state, torch)
+        for value, want in ((None, B.LBM_OK), (-1.0, B.LBM_EPOSITIVITY), (float("nan"), B.LBM_ENONFINITE),
+                            (None, B.LBM_OK), (-1.0, B.LBM_EPOSITIVITY)):
+            s.moments(check=False)  # clears the counters
+            assert s.moments(check=False)[1] == B.LBM_OK
+            state.copy_(good)
+            if value is not None:
+                state[0, 5, 7] = value
+            g.replay()
+            assert s.moments(check=False)[1] == want, value
+        del g, keep
+        s.close()
+
+
+def test_replays_of_a_recorded_load_of_an_ensemble_are_reported(gpu):
+    from paper_2411_15001_amd.solver import BatchSolver
+
+    torch = gpu
+    with torch.cuda.stream(torch.cuda.Stream()):
+        b = BatchSolver([cases.riemann4(n, seed=n) for n in (40, 64, 33)], **KW)
+        good = b.get_state()
+        state = good.clone()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=torch.cuda.current_stream()):
+            b.set_state(state)
+        for bad in (False, True, False, True):
+            b.moments(0, check=False)
+            assert b.moments(0, check=False)[1] == B.LBM_OK
+            state.copy_(good)
+            if bad:
+                state.view(torch.float64)[40 * 40 + 17] = -1.0  # rho of a cell of the second instance
+            g.replay()
+            assert b.moments(0, check=False)[1] == (B.LBM_EPOSITIVITY if bad else B.LBM_OK)
+        del g
+        b.close()
