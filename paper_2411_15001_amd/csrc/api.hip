@@ -741,13 +741,15 @@ lbm_status lbm_moments(lbm_ctx* c, int32_t inst, double* out) {
   } else if (bouchut) {
     res = fail(c, LBM_EBOUCHUT, "the fixed kinetic speed fell below the Bouchut bound");
   }
-  // every counter starts again from zero, behind the read on the stream
+  // every counter starts again from zero; the call waits for that too, so that
+  // neither work of other streams nor a new owner of the workspace meets it
   bool any = false;
   for (const Slots& r : h)
     for (int k = 0; k < vlbm::CNT_N; ++k) any |= r.cnt[k] != 0;
   if (any) {
     const long long records = c->n_inst == 1 ? (long long)((c->lay.red - c->lay.slots) / sizeof(Slots)) : c->n_inst;
     e = vlbm::launch_clear_counts(c->slots, records, c->stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "clearing the counters");
   }
   c->clean = true;

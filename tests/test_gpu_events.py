@@ -83,3 +83,22 @@ def test_replays_of_a_recorded_load_of_an_ensemble_are_reported(gpu):
             assert b.moments(0, check=False)[1] == (B.LBM_EPOSITIVITY if bad else B.LBM_OK)
         del g
         b.close()
+
+
+def test_nothing_is_pending_when_moments_returns(gpu):
+    """The call synchronises with everything it enqueues, the clearing of the
+    counters included."""
+    from paper_2411_15001_amd.solver import Solver
+
+    torch = gpu
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        s = Solver(cases.riemann4(96, seed=6), **KW)
+        out = torch.empty((4, 96, 96), dtype=torch.float64, device="cuda")
+        for _ in range(40):
+            s.step(2)
+            B.lbm_moments(s.ctx, 0, out)
+            assert stream.query()
+        s.step(2)
+        assert s.diagnostics()["n_limited"] > 0  # so every call above had counts to clear
+        s.close()
