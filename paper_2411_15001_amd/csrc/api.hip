@@ -303,12 +303,16 @@ lbm_status upload_tables(lbm_ctx* c) {
   return LBM_OK;
 }
 
-// New strip tables for the current strip height and mode; captured graphs,
-// which hold the old launch, are dropped.
-lbm_status rebuild_launch(lbm_ctx* c) {
-  build_items(c);
+// Captured graphs hold the old launch or boundary descriptions.
+void drop_graphs(lbm_ctx* c) {
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
+}
+
+// New strip tables for the current strip height and mode.
+lbm_status rebuild_launch(lbm_ctx* c) {
+  build_items(c);
+  drop_graphs(c);
   return upload_tables(c);
 }
 
@@ -977,7 +981,11 @@ lbm_status lbm_set_instance_boundary(lbm_ctx* c, int32_t inst, int32_t side, con
       c->has_bnd |= c->bnd[i].kind[k] != nullptr;
       c->has_dirichlet |= c->side_dirichlet[i][k];
     }
-  if (lbm_status st = rebuild_launch(c)) return st;
+  drop_graphs(c);
+  // descriptions come and go with their first and last side; an update of a
+  // moving state, or a further side, keeps the launch and its tables
+  if (!c->manual && default_rows(c) != (c->rows != 0))
+    if (lbm_status st = rebuild_launch(c)) return st;
   if (c->blocked && c->has_bnd) {
     // the kernels that read descriptions take the planar layout: convert the
     // current state once, through the other buffer (which the next step
