@@ -90,8 +90,24 @@ Scheme make_scheme(const lbm_params* p) {
   return s;
 }
 
+// The strip tables a launch can use: of the shape that lbm_get_launch reports
+// (taken once a caller or the tuner has set a shape), of the marches at the
+// height of march_rows, and of the row kernel.  Each has its own memory: steps
+// that a caller recorded keep finding the table they were recorded with, unless
+// a new shape replaces that table itself.
+enum { kGiven, kMarch, kRows, kTables };
+
 struct Layout {
-  size_t slots, shards, red, slots_save, insts, items, bndt, bufA, bufB, theta, total;
+  size_t slots, shards, red, slots_save, insts[kTables], items[kTables], bndt, bufA, bufB, theta, total;
+};
+
+// The instances with their strips of one table, and the instance of every strip
+// (ensembles).
+struct Strips {
+  std::vector<Inst> insts;
+  std::vector<int> item_inst;
+  long long n_items = 0;
+  int rows = 0, mode = 0;  // the height and mode it was built for (0 rows: not yet)
 };
 
 Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
@@ -111,10 +127,12 @@ Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
   o = align_up(o + sizeof(double) * 8 * (size_t)kTotalsBlocks);
   L.slots_save = o;  // the adjoint entry points park the slots here
   o = align_up(o + sizeof(Slots));
-  L.insts = o;
-  o = align_up(o + sizeof(Inst) * (size_t)n);
-  L.items = o;
-  o = align_up(o + sizeof(int) * (size_t)(n > 1 ? items : 0));
+  for (int k = 0; k < kTables; ++k) {  // strip tables of an ensemble
+    L.insts[k] = o;
+    o = align_up(o + sizeof(Inst) * (size_t)(n > 1 ? n : 0));
+    L.items[k] = o;
+    o = align_up(o + sizeof(int) * (size_t)(n > 1 ? items : 0));
+  }
   L.bndt = o;  // boundary descriptions of an ensemble's instances
   o = align_up(o + sizeof(vlbm::BndDesc) * (size_t)(n > 1 ? n : 0));
   L.bufA = o;
@@ -140,10 +158,10 @@ struct lbm_ctx {
   lbm_params p;
   Scheme sc;
   int n_inst = 0;
-  std::vector<Inst> insts;
-  std::vector<int> item_inst;
+  std::vector<Inst> insts;  // (without strips)
+  Strips strips[kTables];
+  int table = kGiven;  // the one that launches use
   long long plane = 0;
-  long long n_items = 0;
   char* ws = nullptr;
   Layout lay;
   Slots* slots = nullptr;
@@ -156,16 +174,12 @@ struct lbm_ctx {
   // every counter is zero: lbm_moments cleared them and nothing that counts
   // was enqueued since
   bool clean = false;
-  Inst* insts_dev = nullptr;
-  int* items_dev = nullptr;
   hipStream_t stream = nullptr;
   hipStream_t cap_stream = nullptr;  // private stream used only to record graphs
   long long step = 0;
   int strip_rows = 64;
   int strip_mode = 0;  // 0: every instance strip_rows; 1: matched to the instance's height
   bool manual = false;  // the launch shape was given by the caller or the tuner
-  int rows = 0;         // steps run the row kernel (see use_rows)
-  int auto_rows = 64;   // rows per strip of the marches while nobody set a shape
   int waves = 4;
   int xcd = 1;
   int grid_per_cu = 0;  // 0: one wave per strip; k > 0: persistent grid of k groups per CU
@@ -190,6 +204,12 @@ struct lbm_ctx {
   void* cur() const { return ws + ((step & 1) ? lay.bufB : lay.bufA); }
   void* other() const { return ws + ((step & 1) ? lay.bufA : lay.bufB); }
   size_t elem() const { return p.precision == LBM_FP64 ? 8 : 4; }
+  const Inst* insts_dev(int k) const { return (const Inst*)(ws + lay.insts[k]); }
+  const int* items_dev(int k) const { return (const int*)(ws + lay.items[k]); }
+  // every table holds the instances' sizes and places
+  const Inst* insts_dev() const { return insts_dev(kGiven); }
+  bool rows() const { return table == kRows; }  // steps run the row kernel (see use_rows)
+  long long n_items() const { return strips[table].n_items; }
 };
 
 namespace {
@@ -207,17 +227,15 @@ lbm_status hip_fail(lbm_ctx* c, hipError_t e, const char* where) {
   return fail(c, LBM_EDEVICE, m);
 }
 
-// Rows per strip of an instance of ny rows.  Mode 0: the context's strip
-// height.  Mode 1 (ensembles of uneven sizes): the tallest power of two that
-// neither exceeds the strip height nor a quarter of the instance's rows (at
-// least kMinStripRows), so that small instances are cut into more, shorter
-// strips while large ones keep tall strips and few re-read halo rows.
-int inst_strip_rows(const lbm_ctx* c, int ny) {
-  if (c->rows) return vlbm::kRowsPerGroup;
-  if (!c->manual) return c->auto_rows;
-  if (c->strip_mode == 0) return c->strip_rows;
+// Rows per strip of an instance of ny rows.  Mode 0: the given height.  Mode 1
+// (ensembles of uneven sizes): the tallest power of two that neither exceeds
+// that height nor a quarter of the instance's rows (at least kMinStripRows), so
+// that small instances are cut into more, shorter strips while large ones keep
+// tall strips and few re-read halo rows.
+int inst_strip_rows(int rows, int mode, int ny) {
+  if (mode == 0) return rows;
   int h = kMinStripRows;
-  while (h * 2 <= c->strip_rows && h * 2 <= ny / 4) h *= 2;
+  while (h * 2 <= rows && h * 2 <= ny / 4) h *= 2;
   return h;
 }
 
@@ -236,42 +254,58 @@ bool default_rows(const lbm_ctx* c) {
   return vlbm::use_rows(strip_rows, c->n_inst, c->has_bnd, c->p.precision, c->sc);
 }
 
-// Rebuild the strip tables after a change of strip height.  Each instance's
-// strips are consecutive work items; in mode 1 the instances with the tallest
-// strips (and, among equal heights, the most rows) come first, so that the
-// longest waves are dispatched first and the short ones fill the end of the
-// launch.
-void build_items(lbm_ctx* c) {
+// Builds strip table k for the height and mode it stands for, unless it is that
+// already, and enqueues its upload (`upload`: whether one was; the vectors must
+// not change before the stream is waited for).  Each instance's strips are
+// consecutive work items; in mode 1 the instances with the tallest strips (and,
+// among equal heights, the most rows) come first, so that the longest waves are
+// dispatched first and the short ones fill the end of the launch.
+lbm_status build_strips(lbm_ctx* c, int k, bool& upload) {
+  Strips& t = c->strips[k];
+  const int rows = k == kRows ? vlbm::kRowsPerGroup : k == kGiven ? c->strip_rows
+    : vlbm::march_rows(c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
+        long long items = 0;
+        for (const Inst& in : c->insts) items += strips_x(in.nx) * strips_y(in.ny, h);
+        return items;
+      });
+  const int mode = k == kGiven ? c->strip_mode : 0;
+  if (t.rows == rows && t.mode == mode) return LBM_OK;
+  t.rows = 0;
+  t.insts = c->insts;
   std::vector<int> order(c->n_inst);
-  c->rows = !c->manual && default_rows(c) ? 1 : 0;
-  c->auto_rows = vlbm::march_rows(c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
-    long long items = 0;
-    for (const Inst& in : c->insts) items += strips_x(in.nx) * strips_y(in.ny, h);
-    return items;
-  });
   for (int i = 0; i < c->n_inst; ++i) {
     order[i] = i;
-    Inst& in = c->insts[i];
-    in.strip_h = inst_strip_rows(c, in.ny);
+    Inst& in = t.insts[i];
+    in.strip_h = inst_strip_rows(rows, mode, in.ny);
     in.xs = (int)strips_x(in.nx);
     in.ys = (int)strips_y(in.ny, in.strip_h);
   }
-  if (c->strip_mode == 1)
-    std::stable_sort(order.begin(), order.end(), [c](int a, int b) {
-      const Inst &x = c->insts[a], &y = c->insts[b];
+  if (mode == 1)
+    std::stable_sort(order.begin(), order.end(), [&t](int a, int b) {
+      const Inst &x = t.insts[a], &y = t.insts[b];
       if (x.strip_h != y.strip_h) return x.strip_h > y.strip_h;
       return x.ny > y.ny;
     });
-  c->n_items = 0;
-  c->item_inst.clear();
+  t.n_items = 0;
+  t.item_inst.clear();
   for (int i : order) {
-    Inst& in = c->insts[i];
-    in.item0 = c->n_items;
-    const long long k = (long long)in.xs * in.ys;
-    if (c->n_inst > 1)
-      for (long long q = 0; q < k; ++q) c->item_inst.push_back(i);
-    c->n_items += k;
+    Inst& in = t.insts[i];
+    in.item0 = t.n_items;
+    t.n_items += (long long)in.xs * in.ys;
+    if (c->n_inst > 1) t.item_inst.resize((size_t)t.n_items, i);
   }
+  if (c->n_inst > 1) {
+    hipError_t e = hipMemcpyAsync((void*)c->insts_dev(k), t.insts.data(), sizeof(Inst) * c->n_inst,
+                                  hipMemcpyHostToDevice, c->stream);
+    if (e == hipSuccess)
+      e = hipMemcpyAsync((void*)c->items_dev(k), t.item_inst.data(), sizeof(int) * t.item_inst.size(),
+                         hipMemcpyHostToDevice, c->stream);
+    if (e != hipSuccess) return hip_fail(c, e, "uploading strip tables");
+    upload = true;
+  }
+  t.rows = rows;
+  t.mode = mode;
+  return LBM_OK;
 }
 
 // The strip height that lbm_get_launch reports for a new context: the tallest
@@ -291,29 +325,24 @@ int default_strip_rows(const lbm_ctx* c) {
   return rows;
 }
 
-lbm_status upload_tables(lbm_ctx* c) {
-  if (c->n_inst == 1) return LBM_OK;
-  hipError_t e = hipMemcpyAsync(c->insts_dev, c->insts.data(), sizeof(Inst) * c->n_inst,
-                                hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess)
-    e = hipMemcpyAsync(c->items_dev, c->item_inst.data(), sizeof(int) * c->item_inst.size(),
-                       hipMemcpyHostToDevice, c->stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
-  if (e != hipSuccess) return hip_fail(c, e, "uploading strip tables");
-  return LBM_OK;
-}
-
 // Captured graphs hold the old launch or boundary descriptions.
 void drop_graphs(lbm_ctx* c) {
   for (auto& kv : c->graphs) (void)hipGraphExecDestroy(kv.second);
   c->graphs.clear();
 }
 
-// New strip tables for the current strip height and mode.
-lbm_status rebuild_launch(lbm_ctx* c) {
-  build_items(c);
+// The launch of the current shape, or, while nobody set one, of the library's
+// choice: the table it uses and the one of the reported shape (which a first
+// lbm_set_grid or lbm_set_launch takes) are in place afterwards.
+lbm_status select_launch(lbm_ctx* c) {
   drop_graphs(c);
-  return upload_tables(c);
+  c->table = c->manual ? kGiven : default_rows(c) ? kRows : kMarch;
+  bool upload = false;
+  lbm_status st = build_strips(c, kGiven, upload);
+  if (st == LBM_OK && c->table != kGiven) st = build_strips(c, c->table, upload);
+  if (st != LBM_OK || !upload) return st;
+  const hipError_t e = hipStreamSynchronize(c->stream);
+  return e == hipSuccess ? LBM_OK : hip_fail(c, e, "uploading strip tables");
 }
 
 // Back to the launch of a new context.
@@ -323,7 +352,7 @@ lbm_status default_launch(lbm_ctx* c) {
   c->strip_mode = 0;
   c->waves = 4;
   c->grid_per_cu = 0;
-  return rebuild_launch(c);
+  return select_launch(c);
 }
 
 // Workgroups of a step launch.  By default one wave per strip, for single
@@ -333,8 +362,8 @@ lbm_status default_launch(lbm_ctx* c) {
 // 256-instance ensemble the persistent grid measured 1-4% slower; the
 // autotuner times both.
 int compute_groups(const lbm_ctx* c) {
-  if (c->rows) return (int)((c->n_items + 7) / 8 * 8);
-  long long g = (c->n_items + c->waves - 1) / c->waves;
+  if (c->rows()) return (int)((c->n_items() + 7) / 8 * 8);
+  long long g = (c->n_items() + c->waves - 1) / c->waves;
   if (c->grid_per_cu > 0) g = std::min(g, (long long)c->grid_per_cu * c->n_cu);
   if (c->xcd) g = (g + 7) / 8 * 8;
   return (int)g;
@@ -349,17 +378,17 @@ vlbm::StepArgs make_args(const lbm_ctx* c, const void* src, void* dst, int slot)
   a.slots = c->slots;
   a.shards = c->shards;
   a.shard_mask = c->n_shards - 1;
-  a.insts = c->insts_dev;
-  a.item_inst = c->n_inst > 1 ? c->items_dev : nullptr;
-  a.inst0 = c->insts[0];
-  a.n_items = c->n_items;
+  a.insts = c->insts_dev(c->table);
+  a.item_inst = c->n_inst > 1 ? c->items_dev(c->table) : nullptr;
+  a.inst0 = c->strips[c->table].insts[0];
+  a.n_items = c->n_items();
   a.n_inst = c->n_inst;
   a.slot = slot;
   a.waves_per_group = c->waves;
   a.xcd_remap = c->xcd;
   a.groups = compute_groups(c);
-  a.rows = c->rows;
-  a.past = vlbm::store_past(c->p.precision, c->plane, !c->ragged, c->rows) ? 1 : 0;
+  a.rows = c->rows() ? 1 : 0;
+  a.past = vlbm::store_past(c->p.precision, c->plane, !c->ragged, c->rows()) ? 1 : 0;
   a.sc = c->sc;
   if (c->n_inst > 1)
     a.bnd_table = (const vlbm::BndDesc*)(c->ws + c->lay.bndt);
@@ -518,8 +547,6 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
   for (int i = 0; i < n; ++i) strips += strips_x(nx[i]) * strips_y(ny[i], kMinStripRows);
   c->n_shards = p->blend == LBM_BLEND_FACE ? vlbm::shards_for(strips / n) : 1;
   c->shards = c->n_shards > 1 ? (Slots*)(c->ws + c->lay.shards) : c->slots;
-  c->insts_dev = (Inst*)(c->ws + c->lay.insts);
-  c->items_dev = (int*)(c->ws + c->lay.items);
   c->insts.resize(n);
   long long off = 0;
   for (int i = 0; i < n; ++i) {
@@ -544,8 +571,7 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
       c->n_cu = cus;
   }
   c->strip_rows = default_strip_rows(c);
-  build_items(c);
-  lbm_status st = upload_tables(c);
+  lbm_status st = select_launch(c);
   if (st != LBM_OK) {
     g_init_error = c->err;
     delete c;
@@ -555,7 +581,7 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
   hipError_t e = vlbm::launch_fill_u32((unsigned int*)c->slots, 0u,
                                        (long long)((c->lay.red - c->lay.slots) / 4), c->stream);
   if (e == hipSuccess)
-    e = vlbm::launch_init(c->sc, c->insts.data(), n, c->insts_dev, c->plane, u0, c->cur(),
+    e = vlbm::launch_init(c->sc, c->insts.data(), n, c->insts_dev(), c->plane, u0, c->cur(),
                           c->slots, p->precision, c->blocked, c->stream);
   if (e != hipSuccess) {
     std::string m = std::string("init launch: ") + hipGetErrorString(e);
@@ -853,7 +879,7 @@ lbm_status lbm_get_state(lbm_ctx* c, void* dst) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (!dst) return fail(c, LBM_EINVAL, "destination must be a device pointer");
   if (lbm_status st = require_attached(c)) return st;
-  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(), dst,
+  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev(), c->n_inst, c->plane, c->cur(), dst,
                                                     c->p.precision, 0, c->stream)
                             : hipMemcpyAsync(dst, c->cur(), lbm_state_bytes(c), hipMemcpyDeviceToDevice,
                                              c->stream);
@@ -865,7 +891,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
   if (!c) return fail(nullptr, LBM_EINVAL, "ctx is NULL");
   if (!src) return fail(c, LBM_EINVAL, "source must be a device pointer");
   if (src == c->cur() || src == c->other()) return fail(c, LBM_EINVAL, "src must be a caller buffer");
-  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, src, c->cur(),
+  hipError_t e = c->blocked ? vlbm::launch_relayout(c->insts.data(), c->insts_dev(), c->n_inst, c->plane, src, c->cur(),
                                                     c->p.precision, 1, c->stream)
                             : hipMemcpyAsync(c->cur(), src, lbm_state_bytes(c), hipMemcpyDeviceToDevice,
                                              c->stream);
@@ -874,7 +900,7 @@ lbm_status lbm_set_state(lbm_ctx* c, const void* src) {
   note_counts(c);  // (non-admissible cells of the state are counted)
   if (e == hipSuccess) e = fold_shards(c, slot);
   if (e == hipSuccess)
-    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(),
+    e = vlbm::launch_lambda_state(c->sc, c->insts.data(), c->insts_dev(), c->n_inst, c->plane, c->cur(),
                                   c->slots, slot, c->p.precision, c->blocked, 1, c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "set_state wavespeed");
   c->detached = false;
@@ -915,7 +941,7 @@ lbm_status lbm_set_launch(lbm_ctx* c, int32_t rows, int32_t waves) {
   if (rows) c->strip_rows = rows;
   if (waves) c->waves = waves;
   if (rows || waves) c->manual = true;
-  return rebuild_launch(c);
+  return select_launch(c);
 }
 
 lbm_status lbm_set_strip_mode(lbm_ctx* c, int32_t mode) {
@@ -923,7 +949,7 @@ lbm_status lbm_set_strip_mode(lbm_ctx* c, int32_t mode) {
   if (mode != 0 && mode != 1) return fail(c, LBM_EINVAL, "strip mode must be 0 or 1");
   c->strip_mode = mode;
   if (mode) c->manual = true;
-  return rebuild_launch(c);
+  return select_launch(c);
 }
 
 lbm_status lbm_set_instance_boundary(lbm_ctx* c, int32_t inst, int32_t side, const uint8_t* kind,
@@ -981,16 +1007,13 @@ lbm_status lbm_set_instance_boundary(lbm_ctx* c, int32_t inst, int32_t side, con
       c->has_bnd |= c->bnd[i].kind[k] != nullptr;
       c->has_dirichlet |= c->side_dirichlet[i][k];
     }
-  drop_graphs(c);
-  // descriptions come and go with their first and last side; an update of a
-  // moving state, or a further side, keeps the launch and its tables
-  if (!c->manual && default_rows(c) != (c->rows != 0))
-    if (lbm_status st = rebuild_launch(c)) return st;
+  // (an update of a moving state, or a further side, keeps the launch)
+  if (lbm_status st = select_launch(c)) return st;
   if (c->blocked && c->has_bnd) {
     // the kernels that read descriptions take the planar layout: convert the
     // current state once, through the other buffer (which the next step
     // overwrites anyway), and stay planar
-    hipError_t e = vlbm::launch_relayout(c->insts.data(), c->insts_dev, c->n_inst, c->plane, c->cur(), c->other(),
+    hipError_t e = vlbm::launch_relayout(c->insts.data(), c->insts_dev(), c->n_inst, c->plane, c->cur(), c->other(),
                                          c->p.precision, 0, c->stream);
     if (e == hipSuccess)
       e = hipMemcpyAsync(c->cur(), c->other(), lbm_state_bytes(c), hipMemcpyDeviceToDevice, c->stream);
@@ -1032,7 +1055,7 @@ lbm_status lbm_set_grid(lbm_ctx* c, int32_t groups_per_cu) {
     return fail(c, LBM_EINVAL, "groups per compute unit must lie in [0, 32]");
   c->grid_per_cu = groups_per_cu;
   if (groups_per_cu) c->manual = true;
-  return rebuild_launch(c);
+  return select_launch(c);
 }
 
 lbm_status lbm_get_grid(const lbm_ctx* c, int32_t* groups_per_cu, int32_t* groups) {
@@ -1113,7 +1136,7 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
     if (s2 != LBM_OK) return s2;
     ms = -1.0f;
     // a persistent grid no smaller than one wave per strip is the same launch
-    if (gpc > 0 && (long long)gpc * c->n_cu * w >= c->n_items) return LBM_OK;
+    if (gpc > 0 && (long long)gpc * c->n_cu * w >= c->n_items()) return LBM_OK;
     vlbm::StepArgs a = make_args(c, c->cur(), c->other(), (int)(c->step % 3));
     // one timed launch sizes the repetition count to about work_ms of work
     hipError_t e = vlbm::launch_step(a, c->p.precision, c->stream);
