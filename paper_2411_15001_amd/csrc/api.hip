@@ -159,6 +159,7 @@ struct lbm_ctx {
   Scheme sc;
   int n_inst = 0;
   std::vector<Inst> insts;  // (without strips)
+  vlbm::Extent extent;
   Strips strips[kTables];
   int table = kGiven;  // the one that launches use
   long long plane = 0;
@@ -249,9 +250,7 @@ lbm_status require_attached(lbm_ctx* c) {
 
 // Whether the default launch of a context is the row kernel's.
 bool default_rows(const lbm_ctx* c) {
-  long long strip_rows = 0;
-  for (const Inst& in : c->insts) strip_rows += strips_x(in.nx) * in.ny;
-  return vlbm::use_rows(strip_rows, c->n_inst, c->has_bnd, c->p.precision, c->sc);
+  return vlbm::use_rows(c->extent, c->has_bnd, c->p.precision, c->sc);
 }
 
 // Builds strip table k for the height and mode it stands for, unless it is that
@@ -560,6 +559,7 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
       return fail(nullptr, LBM_EINVAL, "dx must be > 0");
     }
     off += (long long)nx[i] * ny[i];
+    c->extent.add(nx[i], ny[i]);
   }
   c->plane = off;
   for (const Inst& in : c->insts)

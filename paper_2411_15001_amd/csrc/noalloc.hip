@@ -89,7 +89,9 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   in.nx = p->nx;
   in.ny = p->ny;
   in.xs = (p->nx + 63) / 64;
-  const int rows = vlbm::use_rows((long long)in.xs * p->ny, 1, false, p->precision, sc) ? 1 : 0;
+  vlbm::Extent extent;
+  extent.add(p->nx, p->ny);
+  const int rows = vlbm::use_rows(extent, false, p->precision, sc) ? 1 : 0;
   in.strip_h = rows ? vlbm::kRowsPerGroup
                     : vlbm::march_rows(p->precision, (p->limiters & 6u) != 0 && p->order == 2, [&](int h) {
                         return (long long)in.xs * ((p->ny + h - 1) / h);

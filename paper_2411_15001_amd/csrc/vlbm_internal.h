@@ -144,8 +144,24 @@ inline bool even_rows(const Inst& in, long long plane) { return ((in.nx | in.off
 // Rows of a strip that one workgroup of the row kernel takes, one per wave.
 constexpr int kRowsPerGroup = 4;
 
-// Whether a launch whose shape nobody set takes the row kernel; strip_rows is
-// the number of 64-column strip rows of all instances.  A march needs some
+// Workgroups of 256 threads that one launch can have: its threads must count
+// fewer than 2^32, and the groups are rounded up to the 8 XCDs.
+constexpr long long kMaxGroups = (1ll << 24) - 8;
+
+// What the rules of the launch look at in a context's instances.
+struct Extent {
+  int n_inst = 0;
+  long long strip_rows = 0;  // 64-column strip rows
+  long long row_groups = 0;  // workgroups of the row kernel
+  void add(int nx, int ny) {
+    const long long xs = (nx + 63ll) / 64;
+    n_inst += 1;
+    strip_rows += xs * ny;
+    row_groups += xs * ((ny + kRowsPerGroup - 1) / kRowsPerGroup);
+  }
+};
+
+// Whether a launch whose shape nobody set takes the row kernel.  A march needs some
 // 1024 strips of several rows to fill the chip and spends two (four under
 // density bounds) further rows on each; the row kernel has a wave for every
 // row, evaluates the faces between rows twice and reads its neighbours' rows
@@ -159,12 +175,15 @@ constexpr int kRowsPerGroup = 4;
 // LMP 64 of 40..200 (19502) 113 / 138, 24 of 128..512 187 / 183; float32 PP 88 /
 // 89.4 with 33920 and 112 / 106 with 44544, LMP 105 / 107 and 137 / 126.  With boundary descriptions every row
 // of a march checks for ghosts, here only the rows and strips at the edges:
-// float64 LMP 400^2 32.2 / 63.1, 3000^2 964 / 1145.
-inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, const Scheme& sc) {
+// float64 LMP 400^2 32.2 / 63.1, 3000^2 964 / 1145.  Grids of a few columns and
+// more than 2^26 rows have more groups of four rows than a launch can hold (a
+// march's strips of 64 rows stay below).
+inline bool use_rows(const Extent& x, bool bnd, int precision, const Scheme& sc) {
+  if (x.row_groups > kMaxGroups) return false;
   if (bnd) return true;
   const bool lmp = (sc.limiters & 6) != 0 && sc.order == 2;
-  if (n_inst > 1) return strip_rows <= (precision != 0 ? 36000 : lmp ? 24000 : 57000);
-  return strip_rows <= (precision == 0 ? 13600 : lmp ? 12600 : 16400);
+  if (x.n_inst > 1) return x.strip_rows <= (precision != 0 ? 36000 : lmp ? 24000 : 57000);
+  return x.strip_rows <= (precision == 0 ? 13600 : lmp ? 12600 : 16400);
 }
 
 // Rows per strip of a march whose launch shape nobody set: the height with the
@@ -180,21 +199,24 @@ inline bool use_rows(long long strip_rows, int n_inst, bool bnd, int precision, 
 // strips that fill one round, the rule before, left a nearly empty second
 // round where a little more than one was needed: 1536^2 float64 PP 215 us a
 // step with strips of 32 rows (1.13 rounds), 161 with 12 (3 rounds); 3072^2
-// float32 PP 399 with 64 and 309 with 24; 3072^2 float64 LMP 720 / 604.
+// float32 PP 399 with 64 and 309 with 24; 3072^2 float64 LMP 720 / 604.  Heights
+// whose groups of four waves a launch cannot hold are left out, but for the
+// tallest.
 template <class Strips>
 int march_rows(int precision, bool lmp, const Strips& strips) {
   const double slots = precision == 0 ? 1024.0 : 2048.0;
   const double c = lmp ? 0.44 : (precision == 0 ? 0.54 : 0.48);
   const double e = precision == 0 ? (lmp ? 1.5 : 0.75) : (lmp ? 0.75 : 0.4);
   const double g = precision != 0 && !lmp ? 0.004 : 0.0;
-  int best = 4;
-  double least = 0.0;
+  int best = 64;
+  double least = HUGE_VAL;
   for (int h : {4, 8, 12, 16, 24, 32, 48, 64}) {
+    if (strips(h) > 4 * kMaxGroups) continue;
     const double rounds = (double)strips(h) / slots;
     const double full = __builtin_floor(rounds), phi = rounds - full;
     const double part = phi > 0.0 ? __builtin_cbrt(phi * phi * phi + c * c * c) : 0.0;
     const double t = (full + part) * (h + e) * (1.0 + g * h);
-    if (h == 4 || t <= least) {
+    if (t <= least) {
       least = t;
       best = h;
     }
