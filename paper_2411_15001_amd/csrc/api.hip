@@ -262,7 +262,7 @@ bool default_rows(const lbm_ctx* c) {
 lbm_status build_strips(lbm_ctx* c, int k, bool& upload) {
   Strips& t = c->strips[k];
   const int rows = k == kRows ? vlbm::kRowsPerGroup : k == kGiven ? c->strip_rows
-    : vlbm::march_rows(c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
+    : vlbm::march_rows(c->extent, c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
         long long items = 0;
         for (const Inst& in : c->insts) items += strips_x(in.nx) * strips_y(in.ny, h);
         return items;

@@ -36,7 +36,7 @@ int main() {
     printf("%d %d %lld\n", rows ? 1 : 0, h, (groups + 7) / 8 * 8);
   }
 }
-""".replace("MARCH_ROWS", "vlbm::march_rows(prec, (lims & 6) != 0, strips)")
+""".replace("MARCH_ROWS", "vlbm::march_rows(x, prec, (lims & 6) != 0, strips)")
 
 PP, LMP, RLMP = 9, 11, 13
 
@@ -76,3 +76,36 @@ def test_every_accepted_grid_fits_a_launch(ask):
     for q, (rows, h, groups) in zip(queries, ask(queries)):
         assert 0 < groups * 256 < 1 << 32, q
         assert h in (4, 8, 12, 16, 24, 32, 48, 64), q
+
+
+# us a step on an MI355X at strips of 4 .. 64 rows: (precision, limiters, sizes)
+HEIGHTS = (4, 8, 12, 16, 24, 32, 48, 64)
+MEASURED = [
+    ((0, PP, [(1, 1000000)]), (3914.0, 3049.3, 2760.5, 2622.1, 2472.1, 2409.6, 2368.1, 2362.1)),
+    ((1, PP, [(1, 1000000)]), (2369.2, 1880.6, 1718.8, 1640.3, 1559.2, 1532.3, 1518.6, 1527.7)),
+    ((1, LMP, [(1, 1000000)]), (3259.3, 2385.0, 2099.0, 1969.5, 1821.5, 1769.1, 1736.0, 1737.1)),
+    ((1, PP, [(4, 1000000)]), (2420.8, 1880.6, 1751.9, 1681.3, 1590.2, 1561.9, 1550.6, 1558.4)),
+    ((1, PP, [(20, 200000)]), (508.9, 413.2, 386.9, 374.9, 371.9, 378.3, 403.2, 418.1)),
+    ((1, PP, [(40, 200000)]), (538.9, 456.7, 430.8, 421.5, 424.6, 433.3, 460.1, 462.0)),
+    ((0, LMP, [(70, 100000)]), (1446.1, 1073.8, 966.6, 905.2, 851.8, 830.7, 839.7, 863.8)),
+    ((0, PP, [(100000, 20)]), (194.1, 186.1, 192.3, 229.1, 163.3, 162.8, 162.9, 163.1)),
+    ((1, LMP, [(100000, 20)]), (123.7, 115.8, 118.6, 143.9, 93.7, 93.8, 93.7, 93.7)),
+    ((1, PP, [(32, 32)] * 3000), (261.9, 217.4, 215.5, 194.4, 222.0, 200.0, 201.8, 202.2)),
+    ((1, PP, [(16, 16)] * 5000), (219.7, 177.5, 202.3, 160.8, 161.0, 160.6, 160.3, 160.3)),
+    ((1, PP, [(1, 2048)] * 64), (316.0, 252.5, 238.4, 224.1, 238.2, 215.5, 251.4, 214.5)),
+    ((1, LMP, [(2000, 20)] * 60), (151.6, 133.1, 128.2, 139.7, 105.1, 105.2, 105.0, 104.7)),
+    ((0, PP, [(256, 256)] * 200), (971.5, 849.1, 830.0, 840.9, 855.4, 882.1, 840.5, 926.5)),
+    ((1, LMP, [(256, 256)] * 200), (699.3, 550.8, 521.7, 493.1, 480.3, 489.8, 505.5, 517.1)),
+]
+
+
+@pytest.mark.parametrize("case", MEASURED, ids=lambda c: "p%d_l%d_%dx%dx%d" % (c[0][0], c[0][1], len(c[0][2]), *c[0][2][0]))
+def test_strip_height_of_narrow_and_short_instances(case, ask):
+    """Narrow instances, whose strips leave lanes idle, and instances lower than
+    a strip: the height picked is within 8% of the best that was measured (the
+    tallest strips that fill one round, the shape that lbm_get_launch reports,
+    are up to 54% slower than the best on these)."""
+    (prec, lims, sizes), times = case
+    rows, h, _ = ask([(prec, lims, False, sizes)])[0]
+    assert rows == 0
+    assert times[HEIGHTS.index(h)] <= 1.08 * min(times), h
