@@ -80,9 +80,6 @@ struct StepArgs {
   void* dst;
   long long plane;        // elements per plane (sum of all instances' cells)
   Slots* slots;           // [n_inst]
-  Slots* shards;          // [n_inst][shard_mask + 1]; the slots themselves (mask 0) where
-                          // the launch's records are parked or there are no others
-  int shard_mask;
   const Inst* insts;      // [n_inst], device memory
   const int* item_inst;   // [n_items] instance of every item (batches), or null
   Inst inst0;             // the instance when n_inst == 1
@@ -104,11 +101,19 @@ struct StepArgs {
   int blocked;            // src and dst hold the blocked layout (a context's own
                           // buffers; every width a multiple of 64, no boundary
                           // descriptions), else planar
+  Scheme sc;
+  // (What follows stands at the end because the place of the descriptions above
+  // decides how the compiler groups the loads of a ghost's state: with these
+  // fields ahead of them the described marches loaded one of a halo cell's
+  // twelve values behind the others, 2000^2 float32 PP in strips of 64 rows 378
+  // us a step, so 325.)
   int past;               // 1: the new state is stored past the caches (store_past)
   int rows;               // 1: the row kernel (one row of a strip per wave; the
                           // strips are kRowsPerGroup rows high and groups counts
                           // them), 0: the marches
-  Scheme sc;
+  Slots* shards;          // [n_inst][shard_mask + 1]; the slots themselves (mask 0) where
+                          // the launch's records are parked or there are no others
+  int shard_mask;
 };
 
 // Whether a step stores the new state past the caches (non-temporal) rather than
