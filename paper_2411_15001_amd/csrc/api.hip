@@ -92,10 +92,11 @@ Scheme make_scheme(const lbm_params* p) {
 
 // The strip tables a launch can use: of the shape that lbm_get_launch reports
 // (taken once a caller or the tuner has set a shape), of the marches at the
-// height of march_rows, and of the row kernel.  Each has its own memory: steps
+// height of march_rows, without and with boundary descriptions, and of the row
+// kernel.  Each has its own memory: steps
 // that a caller recorded keep finding the table they were recorded with, unless
 // a new shape replaces that table itself.
-enum { kGiven, kMarch, kRows, kTables };
+enum { kGiven, kMarch, kMarchBnd, kRows, kTables };
 
 struct Layout {
   size_t slots, shards, red, slots_save, insts[kTables], items[kTables], bndt, bufA, bufB, theta, total;
@@ -262,7 +263,7 @@ bool default_rows(const lbm_ctx* c) {
 lbm_status build_strips(lbm_ctx* c, int k, bool& upload) {
   Strips& t = c->strips[k];
   const int rows = k == kRows ? vlbm::kRowsPerGroup : k == kGiven ? c->strip_rows
-    : vlbm::march_rows(c->extent, c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
+    : vlbm::march_rows(c->extent, k == kMarchBnd, c->p.precision, (c->p.limiters & 6u) != 0 && c->p.order == 2, [c](int h) {
         long long items = 0;
         for (const Inst& in : c->insts) items += strips_x(in.nx) * strips_y(in.ny, h);
         return items;
@@ -335,7 +336,7 @@ void drop_graphs(lbm_ctx* c) {
 // lbm_set_grid or lbm_set_launch takes) are in place afterwards.
 lbm_status select_launch(lbm_ctx* c) {
   drop_graphs(c);
-  c->table = c->manual ? kGiven : default_rows(c) ? kRows : kMarch;
+  c->table = c->manual ? kGiven : default_rows(c) ? kRows : c->has_bnd ? kMarchBnd : kMarch;
   bool upload = false;
   lbm_status st = build_strips(c, kGiven, upload);
   if (st == LBM_OK && c->table != kGiven) st = build_strips(c, c->table, upload);

@@ -93,7 +93,7 @@ extern "C" lbm_status lbm_step_noalloc(const lbm_params* p, const void* src_dev,
   extent.add(p->nx, p->ny);
   const int rows = vlbm::use_rows(extent, false, p->precision, sc) ? 1 : 0;
   in.strip_h = rows ? vlbm::kRowsPerGroup
-                    : vlbm::march_rows(extent, p->precision, (p->limiters & 6u) != 0 && p->order == 2, [&](int h) {
+                    : vlbm::march_rows(extent, false, p->precision, (p->limiters & 6u) != 0 && p->order == 2, [&](int h) {
                         return (long long)in.xs * ((p->ny + h - 1) / h);
                       });
   in.ys = (p->ny + in.strip_h - 1) / in.strip_h;

@@ -157,6 +157,7 @@ constexpr long long kMaxGroups = (1ll << 24) - 8;
 struct Extent {
   int n_inst = 0;
   long long strip_rows = 0;  // 64-column strip rows
+  long long edge_rows = 0;   // those that read ghosts (two layers, as under density bounds)
   long long row_groups = 0;  // workgroups of the row kernel
   long long cells = 0;
   int max_ny = 0;
@@ -166,6 +167,8 @@ struct Extent {
     cells += (long long)nx * ny;
     max_ny = ny > max_ny ? ny : max_ny;
     strip_rows += xs * ny;
+    const long long inner = nx >= 130 ? (nx - 66) / 64 : 0;
+    edge_rows += xs * ny - inner * (ny > 4 ? ny - 4 : 0);
     row_groups += xs * ((ny + kRowsPerGroup - 1) / kRowsPerGroup);
   }
 };
@@ -182,15 +185,33 @@ struct Extent {
 // 58 / 49.  Ensembles, whose march strips end ragged at every instance: float64
 // PP 24 of 128..512 (33920 strip rows) 161 / 173, 20 of 200..600 (56415) 260 / 283;
 // LMP 64 of 40..200 (19502) 113 / 138, 24 of 128..512 187 / 183; float32 PP 88 /
-// 89.4 with 33920 and 112 / 106 with 44544, LMP 105 / 107 and 137 / 126.  With boundary descriptions every row
-// of a march checks for ghosts, here only the rows and strips at the edges:
-// float64 LMP 400^2 32.2 / 63.1, 3000^2 964 / 1145.  Grids of a few columns and
-// more than 2^26 rows have more groups of four rows than a launch can hold (a
-// march's strips of 64 rows stay below).
+// 89.4 with 33920 and 112 / 106 with 44544, LMP 105 / 107 and 137 / 126.
+// With boundary descriptions every row of a march looks for ghosts, here only the
+// rows and strips at the edges, but those read them in up to nine chains of loads
+// one after the other, so the share of such rows decides under density bounds
+// (row kernel / best march).  Described on four sides (walls and zero gradient):
+// - PP: 400^2 float64 23 / 58, float32 21 / 57; 64 x 20000 135 / 171, 75 / 104; 256 of
+//   64^2 119 / 118; 8192^2 float64 5144 / 5660.  Large float32 grids are the march's:
+//   3500^2 654 / 647, 4096^2 739 / 743, 5000^2 1305 / 1227, 6000^2 1936 / 1705.
+// - LMP float64: squares 400^2 31 / 82, 2000^2 427 / 478, 8192^2 6423 / 6867; 300 of
+//   64..512 (41% of the rows) 3172 / 3358.  Three strips wide (67%): 130 x 8333 228 /
+//   234, x 33333 875 / 850, x 66666 1753 / 1515.  One or two strips: 64 x 4000 52 / 60,
+//   x 8000 93 / 82, x 100000 988 / 839; 128 of 128^2 317 / 241.
+// - LMP float32: squares 400^2 27 / 72, 2000^2 277 / 284, 3500^2 817 / 775, 4096^2 1018 /
+//   858, 8192^2 4018 / 3434; 500 x 25000 (25%) 988 / 994; 130 x 66666 1031 / 914; one or
+//   two strips 100 x 6000 86 / 97, 64 x 12000 84 / 82, x 25000 155 / 125, x 200000 1172 /
+//   793; 300 of 64..512 1941 / 1765.
+// Grids of a few columns and more than 2^26 rows have more groups of four rows
+// than a launch can hold (a march's strips of 64 rows stay below).
 inline bool use_rows(const Extent& x, bool bnd, int precision, const Scheme& sc) {
   if (x.row_groups > kMaxGroups) return false;
-  if (bnd) return true;
   const bool lmp = (sc.limiters & 6) != 0 && sc.order == 2;
+  if (bnd) {
+    const double rows = (double)x.strip_rows, edge = (double)x.edge_rows / rows;
+    if (!lmp) return precision == 0 || rows <= 300e3;
+    if (precision == 0) return edge <= 0.45 || rows <= 6e3 + 300e3 * (1.0 - edge);
+    return rows <= __builtin_fmin(200e3, 13e3 + 400e3 * (1.0 / edge - 1.0));
+  }
   if (x.n_inst > 1) return x.strip_rows <= (precision != 0 ? 36000 : lmp ? 24000 : 57000);
   return x.strip_rows <= (precision == 0 ? 13600 : lmp ? 12600 : 16400);
 }
@@ -222,11 +243,14 @@ inline bool use_rows(const Extent& x, bool bnd, int precision, const Scheme& sc)
 // 105 / 105; 100000 x 20, float64 PP 194 / 163 / 163.  Over such grids and ensembles and those
 // above, 168 in all, the choice is within 1.5% of the best on average; the
 // choices for the grids above are the same.
+// Nor does memory set the pace with boundary descriptions: n = 1 there, and c is
+// fitted to timings of 130 such grids and ensembles (1% from the best on average:
+// float32 PP 6000^2 1705 us with 48 rows, 1852 with the 12 of the other fit).
 template <class Strips>
-int march_rows(const Extent& x, int precision, bool lmp, const Strips& strips) {
+int march_rows(const Extent& x, bool bnd, int precision, bool lmp, const Strips& strips) {
   const double slots = precision == 0 ? 1024.0 : 2048.0;
-  const double c = lmp ? 0.44 : (precision == 0 ? 0.54 : 0.48);
-  const double n = __builtin_fmax(0.0, 1.0 - (double)x.cells / (64.0 * x.strip_rows) / 0.9);
+  const double c = bnd ? 0.6 : lmp ? 0.44 : (precision == 0 ? 0.54 : 0.48);
+  const double n = bnd ? 1.0 : __builtin_fmax(0.0, 1.0 - (double)x.cells / (64.0 * x.strip_rows) / 0.9);
   const double full = precision == 0 ? (lmp ? 1.5 : 0.75) : (lmp ? 0.75 : 0.4);
   const double e = full + ((lmp ? 3.0 : 2.0) - full) * n;
   const double g = (precision != 0 && !lmp ? 0.004 : 0.0) * (1.0 - n);
