@@ -102,3 +102,26 @@ def test_nothing_is_pending_when_moments_returns(gpu):
         s.step(2)
         assert s.diagnostics()["n_limited"] > 0  # so every call above had counts to clear
         s.close()
+
+
+@pytest.mark.parametrize("n", [24, 64, 100, 150, 200, 330, 512])  # 1 to 32 records an instance
+def test_load_after_steps_folds_every_record(n, gpu):
+    """A load folds the records that the steps before it raised: the counters
+    stay the sum of all of them and lambda becomes the loaded state's."""
+    from paper_2411_15001_amd.solver import BatchSolver, Solver
+
+    u0 = cases.riemann4(n, seed=3)
+    s = Solver(u0, **KW)
+    s.step(5)
+    ref = s.diagnostics()
+    assert ref["n_limited"] > 0
+    s.set_state(s.get_state())
+    got = s.diagnostics()
+    assert all(got[k] == ref[k] for k in ("lam", "t", "n_limited", "n_guard", "n_lmp", "n_bad"))
+    s.close()
+    b = BatchSolver([u0, cases.riemann4(40, seed=4)], **KW)
+    b.step(5)
+    b.set_state(b.get_state())
+    got = b.diagnostics(0)
+    assert all(got[k] == ref[k] for k in ("lam", "n_limited", "n_guard", "n_lmp", "n_bad"))
+    b.close()
