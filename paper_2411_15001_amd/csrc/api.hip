@@ -102,11 +102,11 @@ struct Layout {
   size_t slots, shards, red, slots_save, insts[kTables], items[kTables], bndt, bufA, bufB, theta, total;
 };
 
-// The instances with their strips of one table, and the instance of every strip
-// (ensembles).
+// The instances with their strips of one table; for ensembles also the table's
+// image in the workspace (these, then the instance of every strip).
 struct Strips {
   std::vector<Inst> insts;
-  std::vector<int> item_inst;
+  std::vector<char> image;
   long long n_items = 0;
   int rows = 0, mode = 0;  // the height and mode it was built for (0 rows: not yet)
 };
@@ -255,7 +255,7 @@ bool default_rows(const lbm_ctx* c) {
 }
 
 // Builds strip table k for the height and mode it stands for, unless it is that
-// already, and enqueues its upload (`upload`: whether one was; the vectors must
+// already, and enqueues its upload (`upload`: whether one was; the image must
 // not change before the stream is waited for).  Each instance's strips are
 // consecutive work items; in mode 1 the instances with the tallest strips (and,
 // among equal heights, the most rows) come first, so that the longest waves are
@@ -287,19 +287,19 @@ lbm_status build_strips(lbm_ctx* c, int k, bool& upload) {
       return x.ny > y.ny;
     });
   t.n_items = 0;
-  t.item_inst.clear();
   for (int i : order) {
     Inst& in = t.insts[i];
     in.item0 = t.n_items;
     t.n_items += (long long)in.xs * in.ys;
-    if (c->n_inst > 1) t.item_inst.resize((size_t)t.n_items, i);
   }
   if (c->n_inst > 1) {
-    hipError_t e = hipMemcpyAsync((void*)c->insts_dev(k), t.insts.data(), sizeof(Inst) * c->n_inst,
-                                  hipMemcpyHostToDevice, c->stream);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync((void*)c->items_dev(k), t.item_inst.data(), sizeof(int) * t.item_inst.size(),
-                         hipMemcpyHostToDevice, c->stream);
+    const size_t items = c->lay.items[k] - c->lay.insts[k];
+    t.image.resize(items + sizeof(int) * (size_t)t.n_items);
+    memcpy(t.image.data(), t.insts.data(), sizeof(Inst) * c->n_inst);
+    int* to = (int*)(t.image.data() + items);
+    for (int i : order) to = std::fill_n(to, (long long)t.insts[i].xs * t.insts[i].ys, i);
+    const hipError_t e = hipMemcpyAsync((void*)c->insts_dev(k), t.image.data(), t.image.size(), hipMemcpyHostToDevice,
+                                        c->stream);
     if (e != hipSuccess) return hip_fail(c, e, "uploading strip tables");
     upload = true;
   }
