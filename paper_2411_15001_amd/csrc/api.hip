@@ -99,6 +99,7 @@ Scheme make_scheme(const lbm_params* p) {
 enum { kGiven, kMarch, kMarchBnd, kRows, kTables };
 
 struct Layout {
+  int n_shards;
   size_t slots, shards, red, slots_save, insts[kTables], items[kTables], bndt, bufA, bufB, theta, total;
 };
 
@@ -113,26 +114,30 @@ struct Strips {
 
 Layout layout(const lbm_params* p, int n, const int* nx, const int* ny) {
   const size_t elem = p->precision == LBM_FP64 ? 8 : 4;
-  long long cells = 0, items = 0;
-  for (int i = 0; i < n; ++i) {
-    cells += (long long)nx[i] * ny[i];
-    items += strips_x(nx[i]) * strips_y(ny[i], kMinStripRows);
-  }
+  vlbm::Extent x;
+  for (int i = 0; i < n; ++i) x.add(nx[i], ny[i]);
+  static_assert(vlbm::kRowsPerGroup == kMinStripRows, "no table has more strips than the row kernel groups");
+  const long long cells = x.cells, items = x.row_groups;
+  // the tables that launches of this context can use
+  const Scheme sc = make_scheme(p);
+  const bool rows = vlbm::use_rows(x, false, p->precision, sc), rows_bnd = vlbm::use_rows(x, true, p->precision, sc);
+  const bool used[kTables] = {true, !rows, !rows_bnd, rows || rows_bnd};
   Layout L;
+  L.n_shards = p->blend == LBM_BLEND_FACE ? vlbm::shards_for(x.row_groups / n) : 1;
   size_t o = 0;
   L.slots = o;
   o = align_up(o + sizeof(Slots) * (size_t)n);
   L.shards = o;  // see Slots
-  o = align_up(o + sizeof(Slots) * (size_t)n * vlbm::kShards);
+  o = align_up(o + sizeof(Slots) * (size_t)(L.n_shards > 1 ? (long long)n * L.n_shards : 0));
   L.red = o;  // block partials of lbm_totals and lbm_diagnostics, read with a single instance's records
   o = align_up(o + sizeof(double) * 8 * (size_t)kTotalsBlocks);
   L.slots_save = o;  // the adjoint entry points park the slots here
   o = align_up(o + sizeof(Slots));
   for (int k = 0; k < kTables; ++k) {  // strip tables of an ensemble
     L.insts[k] = o;
-    o = align_up(o + sizeof(Inst) * (size_t)(n > 1 ? n : 0));
+    o = align_up(o + sizeof(Inst) * (size_t)(n > 1 && used[k] ? n : 0));
     L.items[k] = o;
-    o = align_up(o + sizeof(int) * (size_t)(n > 1 ? items : 0));
+    o = align_up(o + sizeof(int) * (size_t)(n > 1 && used[k] ? items : 0));
   }
   L.bndt = o;  // boundary descriptions of an ensemble's instances
   o = align_up(o + sizeof(vlbm::BndDesc) * (size_t)(n > 1 ? n : 0));
@@ -543,9 +548,7 @@ lbm_status common_init(const lbm_params* p, int n, const int32_t* nx, const int3
   c->lay = layout(p, n, nx, ny);
   c->ws = (char*)ws;
   c->slots = (Slots*)(c->ws + c->lay.slots);
-  long long strips = 0;
-  for (int i = 0; i < n; ++i) strips += strips_x(nx[i]) * strips_y(ny[i], kMinStripRows);
-  c->n_shards = p->blend == LBM_BLEND_FACE ? vlbm::shards_for(strips / n) : 1;
+  c->n_shards = c->lay.n_shards;
   c->shards = c->n_shards > 1 ? (Slots*)(c->ws + c->lay.shards) : c->slots;
   c->insts.resize(n);
   long long off = 0;
