@@ -1176,7 +1176,7 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
     (void)hipEventDestroy(e1);
     return s2;
   };
-  if (default_rows(c)) {  // the row kernel (recorded as rows = 0)
+  {  // the library's own choice (recorded as rows = 0)
     float ms = -1.0f;
     st = time_shape(0, 0, 0, 0, 4.0f, ms);
     if (st != LBM_OK) return bail(st);
