@@ -1102,7 +1102,7 @@ lbm_status lbm_autotune(lbm_ctx* c, const char* path) {
         int rows = 0, waves = 0, grid = 0, mode = 0;
         const int got = sscanf(text.c_str() + pos + k.size(), " : [ %d , %d , %d , %d ]", &rows, &waves,
                                &grid, &mode);
-        if (got >= 2 && rows == 0) return default_launch(c);
+        if (got >= 2 && rows == 0 && waves == 0) return default_launch(c);
         if (got >= 2) {
           lbm_status st = lbm_set_launch(c, rows, waves);
           if (st == LBM_OK) st = lbm_set_grid(c, got >= 3 ? grid : 0);

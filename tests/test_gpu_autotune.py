@@ -33,3 +33,30 @@ def test_the_untuned_launch_is_a_candidate(gpu, tmp_path):
     assert entry == [0, 0, 0, 0]
     assert B.lbm_get_grid(s.ctx)[1] == untuned
     s.close()
+
+
+def test_entries_of_the_file(gpu, tmp_path):
+    """[0, 0, ...] is the library's own choice; zero rows with a number of waves
+    keep the current height, as in lbm_set_launch."""
+    from paper_2411_15001_amd.solver import Solver
+
+    u0 = cases.riemann4(96, seed=1)
+    path = str(tmp_path / "tune.json")
+    s = Solver(u0, limiters=9)
+    untuned, shape = B.lbm_get_grid(s.ctx)[1], B.lbm_get_launch(s.ctx)
+    s.autotune(path)
+    s.close()
+    (key,) = json.load(open(path))
+    for entry, launch, groups in (([0, 0, 0, 0], shape, untuned), ([0, 2, 0, 0], (shape[0], 2), None),
+                                  ([8, 2, 0, 0], (8, 2), None)):
+        with open(path, "w") as f:
+            json.dump({key: entry}, f)
+        s = Solver(u0, limiters=9)
+        s.autotune(path)
+        assert B.lbm_get_launch(s.ctx) == launch, entry
+        if groups is not None:
+            assert B.lbm_get_grid(s.ctx)[1] == groups
+        else:
+            strips = 2 * -(-96 // launch[0])
+            assert B.lbm_get_grid(s.ctx)[1] == -(-(-(-strips // launch[1])) // 8) * 8
+        s.close()
