@@ -567,7 +567,7 @@ __device__ void bnd_cell(const StepArgs& A, const BndDesc& bd, const Inst& in, c
 // with the same inputs and code, so both cells of a strip-edge face see the
 // same theta.
 template <class T, class C, int LIMS, bool TH, bool BND, bool NT>
-__device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, int ii, Slots* shard, int xs,
+__device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                             int ys, int lane) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -583,6 +583,9 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
   const int y1 = min(y0 + in.strip_h, ny);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
+  // (with boundary descriptions one pointer takes fewer scalar registers through
+  // the march than what it is computed from)
+  Slots* const shard = BND ? shard_of(A, ii, item) : nullptr;
   const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
 
@@ -814,7 +817,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(shard, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
+  if (lane == 0) publish(BND ? shard : shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
 }
 
 // One aligned strip of the bounds-limited scheme (LMP / RLMP, eq. (29)):
@@ -828,7 +831,7 @@ __device__ __forceinline__ void march_short(const StepArgs& A, const Inst& in, i
 // and lane 0 the west edge face x0 - 1/2, with the same expressions as every
 // other lane, so both strips beside an edge face see the same theta.
 template <class T, class C, int LIMS, bool TH, bool BND, bool NT>
-__device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int ii, Slots* shard, int xs,
+__device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                           int ys, int lane) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -844,6 +847,9 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int
   const int y1 = min(y0 + in.strip_h, ny);
   const bool sponge = LIMS == 0 && sc.sponge > 0;
 
+  // (with boundary descriptions one pointer takes fewer scalar registers through
+  // the march than what it is computed from)
+  Slots* const shard = BND ? shard_of(A, ii, item) : nullptr;
   const double lam = step_lambda(A, ii, lane);
   const StepConst<T, C> K = step_const<T, C>(sc, lam);
 
@@ -1183,7 +1189,7 @@ __device__ __forceinline__ void march_lmp(const StepArgs& A, const Inst& in, int
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(shard, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
+  if (lane == 0) publish(BND ? shard : shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
 }
 
 // ------------------------------------------ bounds-limited march, LDS-staged
@@ -1213,7 +1219,7 @@ typedef __attribute__((address_space(3))) void lds_void;
 // The loads into LDS are not tracked by the compiler's wait counters:
 // the march waits on the vector-memory counter itself (see the loop head).
 template <class T, class C, int LIMS, bool TH, bool BLK, bool NT>
-__device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in, int ii, Slots* shard, int xs,
+__device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                               int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -1535,7 +1541,7 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(shard, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, n_lmp, n_nf, n_rho);
 }
 
 // ------------------------------------------ short march, LDS-staged
@@ -1547,7 +1553,7 @@ __device__ __forceinline__ void march_lmp_dma(const StepArgs& A, const Inst& in,
 // boundary descriptions), where a strip row is one contiguous range; planar
 // states take march_short.
 template <class T, class C, int LIMS, bool TH, bool BLK, bool NT>
-__device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& in, int ii, Slots* shard, int xs,
+__device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& in, int ii, long long item, int xs,
                                                 int ys, int lane, int wave) {
   const Scheme& sc = A.sc;
   const int nx = in.nx, ny = in.ny;
@@ -1772,7 +1778,7 @@ __device__ __forceinline__ void march_short_dma(const StepArgs& A, const Inst& i
   }
   unsigned n_nf, n_rho;
   reduce_classes(n_cls, n_nf, n_rho);
-  if (lane == 0) publish(shard, (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
+  if (lane == 0) publish(shard_of(A, ii, item), (A.slot + 1) % 3, lmax, n_bad, n_guard, n_lim, 0, n_nf, n_rho);
 }
 
 // ------------------------------------------------------------- one row per wave
@@ -2515,15 +2521,14 @@ void step_kernel(StepArgs A) {
     const long long local = item - in.item0;
     const int xs = (int)(local % in.xs);
     const int ys = (int)(local / in.xs);
-    Slots* const shard = shard_of(A, ii, item);  // (one pointer to keep instead of what it takes)
     if constexpr (LMP && DMA)
-      march_lmp_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, shard, xs, ys, lane, wave);
+      march_lmp_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, item, xs, ys, lane, wave);
     else if constexpr (LMP)
-      march_lmp<T, C, LIMS, TH, BND, NT>(A, in, ii, shard, xs, ys, lane);
+      march_lmp<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
     else if constexpr (DMA)
-      march_short_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, shard, xs, ys, lane, wave);
+      march_short_dma<T, C, LIMS, TH, BLK, NT>(A, in, ii, item, xs, ys, lane, wave);
     else
-      march_short<T, C, LIMS, TH, BND, NT>(A, in, ii, shard, xs, ys, lane);
+      march_short<T, C, LIMS, TH, BND, NT>(A, in, ii, item, xs, ys, lane);
   }
 }
 
