@@ -280,7 +280,8 @@ lbm_status lbm_init_adjoint(lbm_ctx* ctx, const double* u0_dev,
 
 /* Times the step kernel for the candidate strip heights, waves per workgroup,
  * grids (one wave per strip, or a persistent grid of 1, 2 or 4 workgroups
- * per compute unit) and, for ensembles, both strip modes on the context's own
+ * per compute unit) and, for ensembles, both strip modes, and the library's own
+ * choice while nobody sets a shape (recorded as zeros), on the context's own
  * problem and keeps the fastest: a first pass times every candidate, then the
  * four fastest are timed again three times, the median decides.  The choice is recorded in a
  * JSON cache file keyed by problem shape (NULL path = no file) as [rows,
@@ -296,7 +297,8 @@ lbm_status lbm_autotune(lbm_ctx* ctx, const char* cache_json_path);
  * tallest strip of 64, 32, 16, 8 or 4 rows that still yields at least 1024
  * (LBM_FP64) or 2048 (LBM_FP32_STATE) strips over all instances; until a call
  * or lbm_autotune sets a shape, grid or strip mode, the library may run the
- * steps in another shape of its own choice.  Results do not depend on it.
+ * steps in another shape of its own choice, which no setting names: giving the
+ * reported values back sets that shape.  Results do not depend on it.
  * Changing the shape drops captured graphs. */
 lbm_status lbm_set_launch(lbm_ctx* ctx, int32_t strip_rows, int32_t waves_per_group);
 lbm_status lbm_get_launch(const lbm_ctx* ctx, int32_t* strip_rows, int32_t* waves_per_group);

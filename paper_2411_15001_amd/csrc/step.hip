@@ -9,8 +9,8 @@
 // the faces and bounds that reach across it.  y-neighbours are the rows the
 // lane already holds in registers from the previous iterations.  No barrier
 // is used; LDS only receives the rows of the LDS-staged marches.  Small grids
-// and described boundaries take the row kernel instead: one row of a strip per
-// wave, its neighbours' rows loaded with it (use_rows for the sizes).
+// and most described boundaries take the row kernel instead: one row of a strip
+// per wave, its neighbours' rows loaded with it (use_rows for the sizes).
 //
 // State layouts.  Planar: value q of cell c (row-major over the instance) at
 // q * plane + c.  Blocked (a context's own buffers when every instance's

@@ -89,7 +89,9 @@ class Solver:
 
     def launch(self):
         """(strip rows, waves per workgroup, groups per CU (0 = one wave per
-        strip), strip mode (1 = heights matched to each instance))"""
+        strip), strip mode (1 = heights matched to each instance)); of a
+        solver whose shape nobody set, the shape that set_launch would start
+        from (its steps may run in another)"""
         return B.lbm_get_launch(self.ctx) + (B.lbm_get_grid(self.ctx)[0], B.lbm_get_strip_mode(self.ctx))
 
     def set_boundary(self, side, kind=None, state=None):
@@ -192,7 +194,9 @@ class BatchSolver:
 
     def launch(self):
         """(strip rows, waves per workgroup, groups per CU (0 = one wave per
-        strip), strip mode (1 = heights matched to each instance))"""
+        strip), strip mode (1 = heights matched to each instance)); of a
+        solver whose shape nobody set, the shape that set_launch would start
+        from (its steps may run in another)"""
         return B.lbm_get_launch(self.ctx) + (B.lbm_get_grid(self.ctx)[0], B.lbm_get_strip_mode(self.ctx))
 
     def set_boundary(self, inst, side, kind=None, state=None):

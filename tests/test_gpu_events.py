@@ -125,3 +125,28 @@ def test_load_after_steps_folds_every_record(n, gpu):
     got = b.diagnostics(0)
     assert all(got[k] == ref[k] for k in ("lam", "n_limited", "n_guard", "n_lmp", "n_bad"))
     b.close()
+
+
+def test_counts_of_every_instance_of_an_ensemble(gpu):
+    """Before any read clears them, each instance's counters, lambda and minima
+    are those of its own run; after the first lbm_moments all start from zero."""
+    from paper_2411_15001_amd.solver import BatchSolver, Solver
+
+    sides = [64, 320, 128, 256, 33]
+    u0s = [cases.riemann4(n, seed=10 + i) for i, n in enumerate(sides)]
+    keys = ("lam", "t", "n_limited", "n_guard", "n_lmp", "n_bad", "min_rho", "min_rhoe")
+    b = BatchSolver(u0s, **KW)
+    runs = [Solver(u0, **KW) for u0 in u0s]
+    for part in (7, 4):
+        b.step(part)
+        for s in runs:
+            s.step(part)
+        for i, s in enumerate(runs):
+            got, ref = b.diagnostics(i), s.diagnostics()
+            assert ref["n_limited"] > 0 and all(got[k] == ref[k] for k in keys), i
+        for i, s in enumerate(runs):
+            assert gpu.equal(b.moments(i), s.moments())
+            assert b.diagnostics(i)["n_limited"] == 0
+    for s in runs:
+        s.close()
+    b.close()
