@@ -190,17 +190,17 @@ struct Extent {
 // rows and strips at the edges, but those read them in up to nine chains of loads
 // one after the other, so the share of such rows decides under density bounds
 // (row kernel / best march).  Described on four sides (walls and zero gradient):
-// - PP: 400^2 float64 23 / 58, float32 21 / 57; 64 x 20000 135 / 171, 75 / 104; 256 of
-//   64^2 119 / 118; 8192^2 float64 5144 / 5660.  Large float32 grids are the march's:
-//   3500^2 654 / 647, 4096^2 739 / 743, 5000^2 1305 / 1227, 6000^2 1936 / 1705.
-// - LMP float64: squares 400^2 31 / 82, 2000^2 427 / 478, 8192^2 6423 / 6867; 300 of
-//   64..512 (41% of the rows) 3172 / 3358.  Three strips wide (67%): 130 x 8333 228 /
-//   234, x 33333 875 / 850, x 66666 1753 / 1515.  One or two strips: 64 x 4000 52 / 60,
-//   x 8000 93 / 82, x 100000 988 / 839; 128 of 128^2 317 / 241.
-// - LMP float32: squares 400^2 27 / 72, 2000^2 277 / 284, 3500^2 817 / 775, 4096^2 1018 /
-//   858, 8192^2 4018 / 3434; 500 x 25000 (25%) 988 / 994; 130 x 66666 1031 / 914; one or
-//   two strips 100 x 6000 86 / 97, 64 x 12000 84 / 82, x 25000 155 / 125, x 200000 1172 /
-//   793; 300 of 64..512 1941 / 1765.
+// - PP: 400^2 float64 18 / 58, float32 13 / 57; 64 x 200000 1179 / 1228, 707 / 655; 256
+//   of 64^2 111 / 118; 8192^2 float64 5381 / 5660.  Large float32 grids are the march's:
+//   3500^2 650 / 647, 4096^2 747 / 743, 5000^2 1301 / 1227, 6000^2 1930 / 1705.
+// - LMP float64: squares 400^2 24 / 82, 2000^2 415 / 478, 8192^2 6584 / 6873; 300 of
+//   64..512 (41% of the rows) 3219 / 3358.  Three strips wide (67%): 130 x 8333 228 /
+//   237, x 33333 897 / 850, x 66666 1809 / 1515.  One or two strips: 64 x 4000 44 / 61,
+//   x 8000 88 / 82, x 100000 1003 / 844; 128 of 64^2 81 / 83, of 128^2 321 / 246.
+// - LMP float32: squares 400^2 19 / 72, 2000^2 267 / 284, 3500^2 814 / 775, 4096^2 1004 /
+//   858, 8192^2 3825 / 3434; 500 x 25000 (25%) 1005 / 994; 130 x 66666 1044 / 914; one or
+//   two strips 100 x 6000 78 / 97, 64 x 12000 74 / 83, x 25000 148 / 126, x 200000 1177 /
+//   793; 300 of 64..512 1953 / 1765.
 // Grids of a few columns and more than 2^26 rows have more groups of four rows
 // than a launch can hold (a march's strips of 64 rows stay below).
 inline bool use_rows(const Extent& x, bool bnd, int precision, const Scheme& sc) {
@@ -209,7 +209,7 @@ inline bool use_rows(const Extent& x, bool bnd, int precision, const Scheme& sc)
   if (bnd) {
     const double rows = (double)x.strip_rows, edge = (double)x.edge_rows / rows;
     if (!lmp) return precision == 0 || rows <= 300e3;
-    if (precision == 0) return edge <= 0.45 || rows <= 6e3 + 300e3 * (1.0 - edge);
+    if (precision == 0) return edge <= 0.45 || rows <= 9e3 + 300e3 * (1.0 - edge);
     return rows <= __builtin_fmin(200e3, 13e3 + 400e3 * (1.0 / edge - 1.0));
   }
   if (x.n_inst > 1) return x.strip_rows <= (precision != 0 ? 36000 : lmp ? 24000 : 57000);

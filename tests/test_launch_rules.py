@@ -114,32 +114,32 @@ def test_strip_height_of_narrow_and_short_instances(case, ask):
 # us a step on an MI355X with descriptions on four sides (walls and zero
 # gradient): (precision, limiters, sizes), the row kernel, marches by strip height
 DESCRIBED = [
-    ((0, LMP, [(1000, 750)]), 80.6, {8: 161.6, 12: 113.7, 16: 134.4, 24: 178.8, 32: 224.2, 48: 317.4, 64: 414.9}),
-    ((1, LMP, [(1000, 750)]), 60.4, {8: 97.4, 12: 105.3, 16: 124.2, 24: 164.5, 32: 206.7, 48: 290.5, 64: 391.6}),
-    ((0, LMP, [(1800, 1800)]), 356.0, {8: 501.4, 12: 485.5, 16: 489.9, 24: 514.2, 32: 447.3, 48: 628.8, 64: 427.4}),
-    ((1, LMP, [(2500, 2500)]), 440.5, {8: 477.9, 12: 457.7, 16: 460.1, 24: 476.2, 32: 481.7, 48: 581.7, 64: 516.9}),
-    ((0, LMP, [(4096, 4096)]), 1693.5, {8: 2321.9, 12: 2150.5, 16: 2012.1, 24: 1985.9, 32: 1854.1, 48: 1975.2, 64: 1774.1}),
-    ((1, LMP, [(4096, 4096)]), 1017.9, {8: 1114.0, 12: 1035.7, 16: 962.5, 24: 945.9, 32: 890.9, 48: 957.9, 64: 857.7}),
-    ((0, LMP, [(8192, 8192)]), 6515.7, {8: 9173.8, 12: 8293.3, 16: 7869.0, 24: 7448.3, 32: 7227.7, 48: 7289.7, 64: 6872.9}),
-    ((1, LMP, [(8192, 8192)]), 4017.5, {8: 4338.0, 12: 3979.6, 16: 3805.1, 24: 3604.7, 32: 3550.4, 48: 3459.2, 64: 3433.7}),
-    ((0, PP, [(8192, 8192)]), 5144.2, {8: 6869.0, 12: 6281.3, 16: 6179.6, 24: 5855.0, 32: 5845.2, 48: 5748.5, 64: 5659.8}),
-    ((1, PP, [(6000, 6000)]), 1936.5, {8: 1989.9, 12: 1852.2, 16: 1777.2, 24: 1724.8, 32: 1718.8, 48: 1704.9, 64: 1739.1}),
-    ((1, PP, [(130, 66666)]), 602.2, {8: 764.0, 12: 729.9, 16: 724.1, 24: 737.6, 32: 761.6, 48: 826.5, 64: 824.0}),
-    ((0, LMP, [(64, 4000)]), 52.4, {4: 61.4, 8: 77.6, 12: 97.0, 16: 118.4, 24: 165.5, 32: 211.5, 48: 299.8, 64: 387.6}),
-    ((1, LMP, [(64, 4000)]), 44.5, {4: 52.6, 8: 64.7, 12: 81.2, 16: 99.4, 24: 143.3, 32: 182.9, 48: 259.9, 64: 337.7}),
-    ((1, LMP, [(64, 12000)]), 84.1, {8: 82.8, 12: 86.8, 16: 102.3, 24: 134.2, 32: 167.6, 48: 248.6, 64: 339.8}),
-    ((0, LMP, [(64, 25000)]), 266.8, {8: 298.7, 12: 300.8, 16: 258.7, 24: 349.0, 32: 236.8, 48: 324.2, 64: 411.3}),
-    ((1, LMP, [(64, 25000)]), 158.9, {8: 148.7, 12: 166.5, 16: 127.0, 24: 171.9, 32: 172.5, 48: 238.9, 64: 318.4}),
-    ((0, LMP, [(128, 50000)]), 986.3, {8: 936.8, 12: 893.4, 16: 874.0, 24: 870.9, 32: 887.8, 48: 957.4, 64: 845.3}),
-    ((1, LMP, [(128, 50000)]), 615.4, {8: 479.1, 12: 451.1, 16: 452.7, 24: 477.3, 32: 450.6, 48: 573.1, 64: 426.7}),
-    ((0, LMP, [(130, 8333)]), 230.8, {8: 304.5, 12: 302.2, 16: 254.2, 24: 349.3, 32: 236.6, 48: 331.1, 64: 424.8}),
-    ((0, LMP, [(130, 66666)]), 1753.2, {8: 1859.9, 12: 1666.9, 16: 1580.6, 24: 1520.0, 32: 1514.8, 48: 1556.0, 64: 1627.1}),
-    ((1, LMP, [(260, 5000)]), 124.4, {8: 162.4, 12: 178.8, 16: 149.2, 24: 196.5, 32: 210.6, 48: 296.0, 64: 389.1}),
-    ((0, LMP, [(64, 64)] * 256), 176.1, {8: 163.2, 12: 202.6, 16: 143.6, 24: 182.9, 32: 224.2, 48: 297.3, 64: 404.1}),
-    ((1, LMP, [(64, 64)] * 256), 114.2, {8: 86.8, 12: 105.6, 16: 109.0, 24: 141.2, 32: 173.6, 48: 242.0, 64: 310.2}),
-    ((0, LMP, [(128, 128)] * 128), 316.8, {4: 397.1, 8: 310.5, 12: 306.9, 16: 270.2, 24: 348.0, 32: 245.8, 48: 328.2, 64: 411.7}),
-    ((1, LMP, [(128, 128)] * 128), 206.7, {4: 210.4, 8: 171.6, 12: 183.6, 16: 145.6, 24: 191.0, 32: 191.4, 48: 259.0, 64: 330.2}),
-    ((0, LMP, [(64, 64)] * 64), 50.2, {4: 61.4, 8: 77.4, 12: 95.7, 16: 116.4, 24: 157.8, 32: 202.8, 48: 276.5, 64: 389.2}),
+    ((0, LMP, [(1000, 750)]), 73.7, {8: 161.6, 12: 113.7, 16: 134.4, 24: 178.8, 32: 224.2, 48: 317.4, 64: 414.9}),
+    ((1, LMP, [(1000, 750)]), 58.7, {8: 97.4, 12: 105.3, 16: 124.2, 24: 164.5, 32: 206.7, 48: 290.5, 64: 391.6}),
+    ((0, LMP, [(1800, 1800)]), 347.4, {8: 501.4, 12: 485.5, 16: 489.9, 24: 514.2, 32: 447.3, 48: 628.8, 64: 427.4}),
+    ((1, LMP, [(2500, 2500)]), 423.5, {8: 477.9, 12: 457.7, 16: 460.1, 24: 476.2, 32: 481.7, 48: 581.7, 64: 516.9}),
+    ((0, LMP, [(4096, 4096)]), 1697.1, {8: 2321.9, 12: 2150.5, 16: 2012.1, 24: 1985.9, 32: 1854.1, 48: 1975.2, 64: 1774.1}),
+    ((1, LMP, [(4096, 4096)]), 1004.3, {8: 1114.0, 12: 1035.7, 16: 962.5, 24: 945.9, 32: 890.9, 48: 957.9, 64: 857.7}),
+    ((0, LMP, [(8192, 8192)]), 6583.6, {8: 9173.8, 12: 8293.3, 16: 7869.0, 24: 7448.3, 32: 7227.7, 48: 7289.7, 64: 6872.9}),
+    ((1, LMP, [(8192, 8192)]), 3824.6, {8: 4338.0, 12: 3979.6, 16: 3805.1, 24: 3604.7, 32: 3550.4, 48: 3459.2, 64: 3433.7}),
+    ((0, PP, [(8192, 8192)]), 5380.6, {8: 6869.0, 12: 6281.3, 16: 6179.6, 24: 5855.0, 32: 5845.2, 48: 5748.5, 64: 5659.8}),
+    ((1, PP, [(6000, 6000)]), 1930.5, {8: 1989.9, 12: 1852.2, 16: 1777.2, 24: 1724.8, 32: 1718.8, 48: 1704.9, 64: 1739.1}),
+    ((1, PP, [(130, 66666)]), 605.9, {8: 764.0, 12: 729.9, 16: 724.1, 24: 737.6, 32: 761.6, 48: 826.5, 64: 824.0}),
+    ((0, LMP, [(64, 4000)]), 44.2, {4: 61.4, 8: 77.6, 12: 97.0, 16: 118.4, 24: 165.5, 32: 211.5, 48: 299.8, 64: 387.6}),
+    ((1, LMP, [(64, 4000)]), 32.7, {4: 52.6, 8: 64.7, 12: 81.2, 16: 99.4, 24: 143.3, 32: 182.9, 48: 259.9, 64: 337.7}),
+    ((1, LMP, [(64, 12000)]), 74.4, {8: 82.8, 12: 86.8, 16: 102.3, 24: 134.2, 32: 167.6, 48: 248.6, 64: 339.8}),
+    ((0, LMP, [(64, 25000)]), 266.0, {8: 298.7, 12: 300.8, 16: 258.7, 24: 349.0, 32: 236.8, 48: 324.2, 64: 411.3}),
+    ((1, LMP, [(64, 25000)]), 148.3, {8: 148.7, 12: 166.5, 16: 127.0, 24: 171.9, 32: 172.5, 48: 238.9, 64: 318.4}),
+    ((0, LMP, [(128, 50000)]), 1021.3, {8: 936.8, 12: 893.4, 16: 874.0, 24: 870.9, 32: 887.8, 48: 957.4, 64: 845.3}),
+    ((1, LMP, [(128, 50000)]), 597.7, {8: 479.1, 12: 451.1, 16: 452.7, 24: 477.3, 32: 450.6, 48: 573.1, 64: 426.7}),
+    ((0, LMP, [(130, 8333)]), 228.0, {8: 304.5, 12: 302.2, 16: 254.2, 24: 349.3, 32: 236.6, 48: 331.1, 64: 424.8}),
+    ((0, LMP, [(130, 66666)]), 1808.6, {8: 1859.9, 12: 1666.9, 16: 1580.6, 24: 1520.0, 32: 1514.8, 48: 1556.0, 64: 1627.1}),
+    ((1, LMP, [(260, 5000)]), 119.6, {8: 162.4, 12: 178.8, 16: 149.2, 24: 196.5, 32: 210.6, 48: 296.0, 64: 389.1}),
+    ((0, LMP, [(64, 64)] * 256), 175.5, {8: 163.2, 12: 202.6, 16: 143.6, 24: 182.9, 32: 224.2, 48: 297.3, 64: 404.1}),
+    ((1, LMP, [(64, 64)] * 256), 106.6, {8: 86.8, 12: 105.6, 16: 109.0, 24: 141.2, 32: 173.6, 48: 242.0, 64: 310.2}),
+    ((0, LMP, [(128, 128)] * 128), 320.7, {4: 397.1, 8: 310.5, 12: 306.9, 16: 270.2, 24: 348.0, 32: 245.8, 48: 328.2, 64: 411.7}),
+    ((1, LMP, [(128, 128)] * 128), 196.8, {4: 210.4, 8: 171.6, 12: 183.6, 16: 145.6, 24: 191.0, 32: 191.4, 48: 259.0, 64: 330.2}),
+    ((0, LMP, [(64, 64)] * 64), 42.0, {4: 61.4, 8: 77.4, 12: 95.7, 16: 116.4, 24: 157.8, 32: 202.8, 48: 276.5, 64: 389.2}),
 ]
 
 
